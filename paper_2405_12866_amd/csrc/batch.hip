@@ -15,6 +15,7 @@
 #include "batch.h"
 #include "philox.h"
 #include "polar2.h"
+#include "polar4.h"
 
 namespace qfs {
 
@@ -150,183 +151,6 @@ __device__ __forceinline__ double dist_states(const cx<R> *x, const c128 *ref, i
     acc += dr * dr + di * di;
   }
   return block_sum<NT>(acc, red) / (double)rows;
-}
-
-// ------------------------------------------------------------------ polar (one wave)
-// Same one-sided Jacobi as the plain path: lane 4c + r holds column c, row r.
-__device__ __forceinline__ c128 bshfl_c(c128 x, int src) {
-  return cmake(__shfl(x.re, src), __shfl(x.im, src));
-}
-__device__ __forceinline__ c128 bquad_sum(c128 x) {
-  x.re += __shfl_xor(x.re, 1);
-  x.im += __shfl_xor(x.im, 1);
-  x.re += __shfl_xor(x.re, 2);
-  x.im += __shfl_xor(x.im, 2);
-  return x;
-}
-
-// u <- polar((1 - beta) G + beta u), warm-started from vst (updated). Writes u64 (global)
-// and u_r (R copy, LDS). Falls back to a serial completion on lane 0 when a singular
-// value vanishes. Called by the 64 lanes of one wave.
-template <typename R>
-__device__ __forceinline__ void batch_polar(const c128 *G, double beta, c128 *u64, cx<R> *u_r, c128 *vst,
-                            c128 *lds_g, c128 *lds_v, double *lds_s) {
-  const int lane = threadIdx.x & 63;
-  const int l = lane & 15, c = l >> 2, r = l & 3, base = lane & ~15;
-  auto gm = [&](int row, int col) {
-    c128 x = G[row * 4 + col];
-    if (beta != 0.0) {
-      const c128 up = u64[row * 4 + col];
-      x = cmake((1.0 - beta) * x.re + beta * up.re, (1.0 - beta) * x.im + beta * up.im);
-    }
-    return x;
-  };
-  // warm start: V_prev made unitary by one Newton-Schulz step, G <- G V_prev
-  const c128 x = vst[r * 4 + c];
-  c128 acc = cmake(0.0, 0.0);
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    const c128 xra = bshfl_c(x, base + 4 * a + r);
-    cfma(acc, xra, bquad_sum(cconj(xra) * x));
-  }
-  c128 v = cmake(0.5 * (3.0 * x.re - acc.re), 0.5 * (3.0 * x.im - acc.im));
-  c128 g = cmake(0.0, 0.0);
-#pragma unroll
-  for (int k = 0; k < 4; ++k) cfma(g, gm(r, k), bshfl_c(v, base + 4 * c + k));
-  bool converged = false;
-  for (int sweep = 0; sweep < 40; ++sweep) {
-    int rotated = 0;
-#pragma unroll
-    for (int m = 4; m <= 12; m += 4) {
-      const c128 go = cmake(__shfl_xor(g.re, m), __shfl_xor(g.im, m));
-      const c128 vo = cmake(__shfl_xor(v.re, m), __shfl_xor(v.im, m));
-      const bool is_p = (l ^ m) > l;
-      const c128 gp = is_p ? g : go, gq = is_p ? go : g;
-      const c128 vp = is_p ? v : vo, vq = is_p ? vo : v;
-      double al = cabs2(gp), be = cabs2(gq);
-      double gr = gp.re * gq.re + gp.im * gq.im;
-      double gi = gp.re * gq.im - gp.im * gq.re;
-#pragma unroll
-      for (int o = 1; o <= 2; o <<= 1) {
-        al += __shfl_xor(al, o);
-        be += __shfl_xor(be, o);
-        gr += __shfl_xor(gr, o);
-        gi += __shfl_xor(gi, o);
-      }
-      const double ag = sqrt(gr * gr + gi * gi);
-      if (ag > 0.0 && ag > 1e-15 * sqrt(al * be)) {
-        rotated = 1;
-        const c128 ec = cmake(gr / ag, -gi / ag);
-        const double tau = (be - al) / (2.0 * ag);
-        const double tt = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-        const double cs = 1.0 / sqrt(1.0 + tt * tt), sn = cs * tt;
-        const c128 egq = ec * gq, evq = ec * vq;
-        if (is_p) {
-          g = cmake(cs * gp.re - sn * egq.re, cs * gp.im - sn * egq.im);
-          v = cmake(cs * vp.re - sn * evq.re, cs * vp.im - sn * evq.im);
-        } else {
-          g = cmake(sn * gp.re + cs * egq.re, sn * gp.im + cs * egq.im);
-          v = cmake(sn * vp.re + cs * evq.re, sn * vp.im + cs * evq.im);
-        }
-      }
-    }
-    if (!__any(rotated)) {
-      converged = true;
-      break;
-    }
-  }
-  double s2 = cabs2(g);
-  s2 += __shfl_xor(s2, 1);
-  s2 += __shfl_xor(s2, 2);
-  const double sig = sqrt(s2);
-  double smin = fmin(sig, __shfl_xor(sig, 4)), smax = fmax(sig, __shfl_xor(sig, 4));
-  smin = fmin(smin, __shfl_xor(smin, 8));
-  smax = fmax(smax, __shfl_xor(smax, 8));
-  if (converged && smin > 1e-200 && smin > 1e-15 * smax) {
-    const c128 w = cscale(g, 1.0 / sig);
-    const int q = l >> 2, p = l & 3;
-    c128 u = cmake(0.0, 0.0);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) cfma_conj(u, bshfl_c(w, base + 4 * k + q), bshfl_c(v, base + 4 * k + p));
-    if (lane < 16) {
-      u64[l] = u;
-      u_r[l] = cmake<R>((R)u.re, (R)u.im);
-      vst[r * 4 + c] = v;
-    }
-    return;
-  }
-  if (lane < 16) {
-    lds_g[c * 4 + r] = g;
-    lds_v[c * 4 + r] = v;
-    if (r == 0) lds_s[c] = sig;
-    vst[r * 4 + c] = v;
-  }
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  if (lane == 0) {
-    int ord[4] = {0, 1, 2, 3};
-    for (int a = 0; a < 4; ++a)
-      for (int b = a + 1; b < 4; ++b)
-        if (lds_s[ord[b]] > lds_s[ord[a]]) {
-          const int t = ord[a];
-          ord[a] = ord[b];
-          ord[b] = t;
-        }
-    const double sm = lds_s[ord[0]];
-    c128 w[4][4];
-    for (int k = 0; k < 4; ++k) {
-      const int cc = ord[k];
-      const double sk = lds_s[cc];
-      c128 xx[4];
-      bool ok = sk > 0.0 && sk > 1e-13 * sm;
-      if (ok) {
-        for (int rr = 0; rr < 4; ++rr) xx[rr] = cscale(lds_g[cc * 4 + rr], 1.0 / sk);
-        for (int rep = 0; rep < 2; ++rep)
-          for (int o = 0; o < k; ++o) {
-            c128 d = cmake(0.0, 0.0);
-            for (int rr = 0; rr < 4; ++rr) cfma(d, cconj(w[o][rr]), xx[rr]);
-            for (int rr = 0; rr < 4; ++rr) xx[rr] = xx[rr] - d * w[o][rr];
-          }
-        double nn = 0.0;
-        for (int rr = 0; rr < 4; ++rr) nn += cabs2(xx[rr]);
-        nn = sqrt(nn);
-        if (nn > 0.5)
-          for (int rr = 0; rr < 4; ++rr) xx[rr] = cscale(xx[rr], 1.0 / nn);
-        else
-          ok = false;
-      }
-      if (!ok) {
-        double best = -1.0;
-        c128 bx[4];
-        for (int e = 0; e < 4; ++e) {
-          c128 y[4];
-          for (int rr = 0; rr < 4; ++rr) y[rr] = cmake(rr == e ? 1.0 : 0.0, 0.0);
-          for (int rep = 0; rep < 2; ++rep)
-            for (int o = 0; o < k; ++o) {
-              c128 d = cmake(0.0, 0.0);
-              for (int rr = 0; rr < 4; ++rr) cfma(d, cconj(w[o][rr]), y[rr]);
-              for (int rr = 0; rr < 4; ++rr) y[rr] = y[rr] - d * w[o][rr];
-            }
-          double nn = 0.0;
-          for (int rr = 0; rr < 4; ++rr) nn += cabs2(y[rr]);
-          if (nn > best) {
-            best = nn;
-            for (int rr = 0; rr < 4; ++rr) bx[rr] = y[rr];
-          }
-        }
-        const double inv = 1.0 / sqrt(best);
-        for (int rr = 0; rr < 4; ++rr) xx[rr] = cscale(bx[rr], inv);
-      }
-      for (int rr = 0; rr < 4; ++rr) w[k][rr] = xx[rr];
-    }
-    for (int q = 0; q < 4; ++q)
-      for (int p = 0; p < 4; ++p) {
-        c128 u = cmake(0.0, 0.0);
-        for (int k = 0; k < 4; ++k) cfma_conj(u, w[k][q], lds_v[ord[k] * 4 + p]);
-        u64[q * 4 + p] = u;
-        u_r[q * 4 + p] = cmake<R>((R)u.re, (R)u.im);
-      }
-  }
 }
 
 // ------------------------------------------------------------------ job sweeps
@@ -479,7 +303,7 @@ __device__ void run_job(const BatchArgs &A, int jid, cx<R> *bufA, cx<R> *bufB,
       if (kind == QFS_GATE_1Q) {
         if (threadIdx.x == 0) polar2_update<R>(sh.gam, beta, g64 + k * 16, unew);
       } else if (threadIdx.x < 64) {
-        batch_polar<R>(sh.gam, beta, g64 + k * 16, unew, vst + k * 16, sh.pg, sh.pv, sh.ps);
+        polar4_wave<R>(sh.gam, beta, g64 + k * 16, g64 + k * 16, unew, sh.pg, sh.pv, sh.ps, vst + k * 16);
       }
       __syncthreads();
     }

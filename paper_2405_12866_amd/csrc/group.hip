@@ -367,22 +367,30 @@ __global__ __launch_bounds__(kGBlock) void k_bwd_group(GroupArgs<R> A) {
 
 struct GroupFin {
   int32_t k_hi, k_lo, nvar;
-  int32_t sa[kGroupMaxGates], sb[kGroupMaxGates];  // slots of gate k_lo + i's qubits
-  int32_t kind[kGroupMaxGates];
+  int32_t i_last;                // the lowest variable gate (k_lo + i_last): R is not needed below
+  int32_t slot[kGroupMaxGates];  // gate k_lo + i: slots of its qubits and kind, a | b << 2 | kind << 4
 };
 
 // Per start: fixed-order FP64 sum of the block partials of G, then the group's gates from
-// the top down: Gamma_k by partial trace of H_k, u_k <- polar((1 - beta) Gamma_k + beta u_k)
-// (one wave; one-qubit slots by the closed-form 2x2 update), H_{k-1} = u_k^dag H_k u_{k-1}.
-// Also the group's operator Vop = u_{k_lo}^dag ... u_{k_hi}^dag over its four slots (the
-// updated gates), which the next pass applies to the backward state.
-__global__ __launch_bounds__(256) void k_group_finalize(const c128 *partials, int P, int pstride,
-                                                        const int32_t *slot_to_start, GroupFin F,
-                                                        double beta, c128 *g64, c64 *g32,
-                                                        int32_t gstride, c128 *vstore, c128 *vop) {
-  __shared__ c128 H[256], Vm[256];
+// the top down. With R_k = G W_k^dag (W_k: the pre-sweep gates below k) and V_k the daggers of
+// the updated gates above k,
+//   Gamma_k[q][p] = sum_s (V_k R_k)[(q, s)][(p, s)],   u_k <- polar((1 - beta) Gamma_k + beta u_k)
+// (one wave; one-qubit slots by the closed-form 2x2 update), V_{k-1} = u_k^dag V_k and
+// R_{k-1} = R_k u_{k-1}. R depends on no updated gate, so the other waves form R_{k-1} while
+// wave 0 updates gate k, and the serial chain per gate is Gamma, polar factor, V: three
+// barriers. V at the end is the group's operator Vop = u_{k_lo}^dag ... u_{k_hi}^dag, which the
+// next pass applies to the backward state.
+// Bound by that chain (one work-group per start): of about 7.6 us for a group of two gates
+// (9.3 with H updated in place by four barriers per product, 14.0 with the Jacobi SVD as
+// well) some 2 are the launch, 2 the loads and the partial sums, 1.7 each gate's polar factor.
+__global__ __launch_bounds__(256, 4) void k_group_finalize(const c128 *partials, int P, int pstride,
+                                                           const int32_t *slot_to_start, GroupFin F,
+                                                           double beta, c128 *g64, c64 *g32,
+                                                           int32_t gstride, c128 *vstore, c128 *vop) {
+  // rows of 17 entries: a column of a matrix falls on different LDS banks
+  constexpr int W = 17;
+  __shared__ c128 Rm[2][16 * W], Vm[2][16 * W];
   __shared__ c128 ug[kGroupMaxGates][16];  // the group's gates (pre-sweep, then updated)
-  __shared__ c128 vw[kGroupMaxGates][16];  // their Jacobi warm starts
   __shared__ c128 gam[16];
   __shared__ c128 pg[16], pv[16];
   __shared__ double psig[4];
@@ -391,108 +399,104 @@ __global__ __launch_bounds__(256) void k_group_finalize(const c128 *partials, in
   const int z = t >> 4, y = t & 15;
   const int ngate = F.k_hi - F.k_lo + 1;
   c128 *gs = g64 + (int64_t)s * gstride;
-  if (t < 16 * ngate) {
-    ug[t >> 4][t & 15] = gs[(F.k_lo + (t >> 4)) * 16 + (t & 15)];
-    if (vstore) vw[t >> 4][t & 15] = vstore[(int64_t)s * gstride + (F.k_lo + (t >> 4)) * 16 + (t & 15)];
-  }
+  if (t < 16 * ngate) ug[t >> 4][t & 15] = gs[(F.k_lo + (t >> 4)) * 16 + (t & 15)];
   if (F.nvar > 0) {
-    // fixed-order sum of the block partials: eight interleaved accumulators, each batch of
-    // eight loads in flight together
+    // fixed-order sum of the block partials: sixteen loads in flight, eight running sums
     const c128 *src = partials + (int64_t)s * pstride * 256 + t;
     c128 acc[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) acc[u] = cmake(0.0, 0.0);
     int p = 0;
-    for (; p + 7 < P; p += 8) {
-      c128 v[8];
+    for (; p + 15 < P; p += 16) {
+      c128 v[16];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = src[(int64_t)(p + u) * 256];
+      for (int u = 0; u < 16; ++u) v[u] = src[(int64_t)(p + u) * 256];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) acc[u] = acc[u] + v[u];
+      for (int u = 0; u < 16; ++u) acc[u & 7] = acc[u & 7] + v[u];
     }
 #pragma unroll
-    for (int u = 0; u < 7; ++u)
-      if (p + u < P) acc[u] = acc[u] + src[(int64_t)(p + u) * 256];
-    H[t] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
+    for (int u = 0; u < 15; ++u)
+      if (p + u < P) acc[u & 7] = acc[u & 7] + src[(int64_t)(p + u) * 256];
+    Rm[0][z * W + y] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
   }
-  Vm[t] = cmake(z == y ? 1.0 : 0.0, 0.0);
-  // X <- X op(u) with u on slots (a, b) of the column index; op(u) = u^dag or u
-  auto right = [&](c128 *X, const c128 *u, int a, int b, bool dag) {
-    const int ly = 2 * ((y >> a) & 1) + ((y >> b) & 1);
-    const int yb = y & ~((1 << a) | (1 << b));
+  Vm[0][z * W + y] = cmake(z == y ? 1.0 : 0.0, 0.0);
+  // entry (row, col) of X op(u) with u on slots (a, b) of the column index; op(u) = u^dag or u
+  auto right = [&](const c128 *X, const c128 *u, int a, int b, bool dag, int row, int col) -> c128 {
+    const int ly = 2 * ((col >> a) & 1) + ((col >> b) & 1);
+    const c128 *x = X + row * W + (col & ~((1 << a) | (1 << b)));
     c128 v = cmake(0.0, 0.0);
 #pragma unroll
-    for (int p2 = 0; p2 < 4; ++p2) {
-      const int yy = yb | ((p2 >> 1) << a) | ((p2 & 1) << b);
-      const c128 m = dag ? cconj(u[ly * 4 + p2]) : u[p2 * 4 + ly];
-      cfma(v, X[z * 16 + yy], m);
-    }
-    __syncthreads();
-    X[t] = v;
-    __syncthreads();
+    for (int p2 = 0; p2 < 4; ++p2)
+      cfma(v, x[((p2 >> 1) << a) | ((p2 & 1) << b)], dag ? cconj(u[ly * 4 + p2]) : u[p2 * 4 + ly]);
+    return v;
   };
-  // X <- u^dag X (and Y <- u^dag Y when given) with u on slots (a, b) of the row index
-  auto left_dag = [&](c128 *X, c128 *Y, const c128 *u, int a, int b) {
-    const int lz = 2 * ((z >> a) & 1) + ((z >> b) & 1);
-    const int zb = z & ~((1 << a) | (1 << b));
-    c128 v = cmake(0.0, 0.0), w = cmake(0.0, 0.0);
-#pragma unroll
-    for (int q2 = 0; q2 < 4; ++q2) {
-      const int zz = zb | ((q2 >> 1) << a) | ((q2 & 1) << b);
-      const c128 m = cconj(u[q2 * 4 + lz]);
-      cfma(v, m, X[zz * 16 + y]);
-      if (Y) cfma(w, m, Y[zz * 16 + y]);
-    }
-    __syncthreads();
-    X[t] = v;
-    if (Y) Y[t] = w;
-    __syncthreads();
-  };
-  __syncthreads();
-  // H_{k_hi} = G W^dag, W = u_{k_hi - 1} ... u_{k_lo} (pre-sweep gates)
+  lds_barrier();
+  // R_{k_hi} = G W^dag, W = u_{k_hi - 1} ... u_{k_lo} (pre-sweep gates)
+  int rc = 0, vc = 0;  // current buffers of R and V
   if (F.nvar > 0)
-    for (int k = F.k_lo; k < F.k_hi; ++k) right(H, ug[k - F.k_lo], F.sa[k - F.k_lo], F.sb[k - F.k_lo], true);
-  // the variable gate lowest in the group: H is not needed below it
-  int k_last = F.k_lo;
-  while (k_last < F.k_hi && F.kind[k_last - F.k_lo] == QFS_GATE_FIXED) ++k_last;
-  for (int k = F.k_hi; k >= F.k_lo; --k) {
-    const int i = k - F.k_lo;
-    const int a = F.sa[i], b = F.sb[i];
-    if (F.kind[i] != QFS_GATE_FIXED) {
-      if (t < 16) {
-        // Gamma[q][p] = sum over the two other slots o0 < o1 of H[(q, o)][(p, o)]
-        const int om = 15 & ~((1 << a) | (1 << b));
-        const int o0 = __ffs(om) - 1, o1 = __ffs(om & (om - 1)) - 1;
-        const int qq = t >> 2, pp = t & 3;
-        const int zq = ((qq >> 1) << a) | ((qq & 1) << b), zp = ((pp >> 1) << a) | ((pp & 1) << b);
-        c128 g = cmake(0.0, 0.0);
-#pragma unroll
-        for (int s2 = 0; s2 < 4; ++s2) {
-          const int zo = ((s2 >> 1) << o0) | ((s2 & 1) << o1);
-          g = g + H[(zq | zo) * 16 + (zp | zo)];
-        }
-        gam[t] = g;
-      }
-      __syncthreads();
-      if (t < 64) {
-        if (F.kind[i] == QFS_GATE_1Q) {
-          if (t == 0) polar2_update<float>(gam, beta, ug[i], nullptr);
-        } else {
-          polar4_wave(gam, beta, gs + k * 16, ug[i], nullptr, pg, pv, psig,
-                      vstore ? vstore + (int64_t)s * gstride + k * 16 : nullptr, vw[i]);
-        }
-      }
-      __syncthreads();
-      if (t < 16) {
-        gs[k * 16 + t] = ug[i][t];
-        if (g32) g32[(int64_t)s * gstride + k * 16 + t] = cmake<float>((float)ug[i][t].re, (float)ug[i][t].im);
-      }
+    for (int i = 0; i < ngate - 1; ++i) {
+      Rm[rc ^ 1][z * W + y] = right(Rm[rc], ug[i], F.slot[i] & 3, (F.slot[i] >> 2) & 3, true, z, y);
+      rc ^= 1;
+      lds_barrier();
     }
-    const bool more = F.nvar > 0 && k > k_last;
-    left_dag(Vm, more ? H : nullptr, ug[i], a, b);
-    if (more) right(H, ug[i - 1], F.sa[i - 1], F.sb[i - 1], false);
+  // (the slots and the kind of a gate, packed, are read one gate ahead: a scalar load from
+  // the kernel arguments would otherwise stand in the chain)
+  int cur = F.slot[ngate - 1];
+  for (int i = ngate - 1; i >= 0; --i) {
+    const int a = cur & 3, b = (cur >> 2) & 3, kind = cur >> 4;
+    const int below = F.slot[i > 0 ? i - 1 : 0];
+    const int k = F.k_lo + i;
+    const bool more = F.nvar > 0 && i > F.i_last;
+    const bool var = kind != QFS_GATE_FIXED;
+    if (var) {
+      // thread 16 (4 q + p) + 4 s + w4: the terms w = w4, w4 + 4, .. of
+      // sum_w V[(q, s)][w] R[w][(p, s)], summed over the row's 16 lanes
+      const int om = 15 & ~((1 << a) | (1 << b));
+      const int o0 = __ffs(om) - 1, o1 = __ffs(om & (om - 1)) - 1;
+      const int qq = t >> 6, pp = (t >> 4) & 3, s2 = (t >> 2) & 3, w0 = t & 3;
+      const int zo = ((s2 >> 1) << o0) | ((s2 & 1) << o1);
+      const int zr = ((qq >> 1) << a) | ((qq & 1) << b) | zo, zc = ((pp >> 1) << a) | ((pp & 1) << b) | zo;
+      c128 g = cmake(0.0, 0.0);
+#pragma unroll
+      for (int w = 0; w < 16; w += 4) cfma(g, Vm[vc][zr * W + w0 + w], Rm[rc][(w0 + w) * W + zc]);
+      g.re = row16_sum(g.re);
+      g.im = row16_sum(g.im);
+      if ((t & 15) == 0) gam[t >> 4] = g;
+      lds_barrier();
+    }
+    if (t >= 64) {
+      if (more)
+        for (int e = t - 64; e < 256; e += 192)
+          Rm[rc ^ 1][(e >> 4) * W + (e & 15)] =
+              right(Rm[rc], ug[i - 1], below & 3, (below >> 2) & 3, false, e >> 4, e & 15);
+    } else if (kind == QFS_GATE_1Q) {
+      if (t == 0) polar2_update<float>(gam, beta, ug[i], nullptr);
+    } else if (var) {
+      polar4_wave<float>(gam, beta, gs + k * 16, ug[i], nullptr, pg, pv, psig,
+                         vstore ? vstore + (int64_t)s * gstride + k * 16 : nullptr);
+    }
+    lds_barrier();
+    if (more) rc ^= 1;
+    {
+      // V <- u^dag V with u on slots (a, b) of the row index
+      const int lz = 2 * ((z >> a) & 1) + ((z >> b) & 1);
+      const int zb = z & ~((1 << a) | (1 << b));
+      c128 v = cmake(0.0, 0.0);
+#pragma unroll
+      for (int q2 = 0; q2 < 4; ++q2)
+        cfma(v, cconj(ug[i][q2 * 4 + lz]), Vm[vc][(zb | ((q2 >> 1) << a) | ((q2 & 1) << b)) * W + y]);
+      Vm[vc ^ 1][z * W + y] = v;
+      vc ^= 1;
+    }
+    lds_barrier();
+    cur = below;
   }
-  vop[(int64_t)s * 256 + t] = Vm[t];
+  if (t < 16 * ngate && (F.slot[t >> 4] >> 4) != QFS_GATE_FIXED) {
+    const c128 u = ug[t >> 4][t & 15];
+    gs[(F.k_lo + (t >> 4)) * 16 + (t & 15)] = u;
+    if (g32) g32[(int64_t)s * gstride + (F.k_lo + (t >> 4)) * 16 + (t & 15)] = cmake<float>((float)u.re, (float)u.im);
+  }
+  vop[(int64_t)s * 256 + t] = Vm[vc][z * W + y];
 }
 
 // ------------------------------------------------------------------ grouped forward pass
@@ -980,10 +984,11 @@ int launch_group_finalize(int P, const c128 *gpartials, int pstride, const int32
       if (cur.q[i] == q) return i;
     return -1;
   };
-  for (int k = cur.k_lo; k <= cur.k_hi; ++k) {
-    F.sa[k - cur.k_lo] = slot(pairs[2 * k]);
-    F.sb[k - cur.k_lo] = slot(pairs[2 * k + 1]);
-    F.kind[k - cur.k_lo] = kinds ? kinds[k] : QFS_GATE_2Q;
+  F.i_last = cur.k_hi - cur.k_lo;
+  for (int k = cur.k_hi; k >= cur.k_lo; --k) {
+    const int kind = kinds ? kinds[k] : QFS_GATE_2Q;
+    F.slot[k - cur.k_lo] = slot(pairs[2 * k]) | slot(pairs[2 * k + 1]) << 2 | kind << 4;
+    if (kind != QFS_GATE_FIXED) F.i_last = k - cur.k_lo;
   }
   hipExtLaunchKernelGGL(k_group_finalize, dim3(nslots), dim3(256), 0, s, ev.start, ev.stop, 0, gpartials, P,
                         pstride, slot_to_start, F, beta, g64, g32, gstride, vstore, vop);

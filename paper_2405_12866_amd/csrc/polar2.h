@@ -1,7 +1,7 @@
 // Update of a variable one-qubit gate, shared by the plain and the batched engines.
 #pragma once
 
-#include "qfs_internal.h"
+#include "polar4.h"
 
 namespace qfs {
 
@@ -25,14 +25,16 @@ __device__ inline void polar2_update(const c128 *G, double beta, c128 *u64, cx<R
       x[q * 2 + p] = cscale(g1, 1.0 - beta) + cscale(u64[(2 * q) * 4 + 2 * p], beta);
     }
   const c128 det = x[0] * x[3] - x[1] * x[2];
-  const double ad = sqrt(cabs2(det));
-  const c128 w = ad > 0.0 ? cscale(det, 1.0 / ad) : cmake(1.0, 0.0);
+  // 1 / |det| and 1 / norm by rsq_nr: about one ulp, and a short chain (this runs on one thread)
+  const double d2 = cabs2(det);
+  const c128 w = d2 > 0.0 ? cscale(det, rsq_nr(d2)) : cmake(1.0, 0.0);
   c128 y[4] = {x[0] + w * cconj(x[3]), x[1] - w * cconj(x[2]), x[2] - w * cconj(x[1]),
                x[3] + w * cconj(x[0])};
-  const double nrm = sqrt((cabs2(y[0]) + cabs2(y[1]) + cabs2(y[2]) + cabs2(y[3])) * 0.5);
-  if (!(nrm > 0.0)) return;
+  const double n2 = ((cabs2(y[0]) + cabs2(y[1])) + (cabs2(y[2]) + cabs2(y[3]))) * 0.5;
+  if (!(n2 > 0.0)) return;
+  const double inv = rsq_nr(n2);
 #pragma unroll
-  for (int e = 0; e < 4; ++e) y[e] = cscale(y[e], 1.0 / nrm);
+  for (int e = 0; e < 4; ++e) y[e] = cscale(y[e], inv);
 #pragma unroll
   for (int r = 0; r < 4; ++r)
 #pragma unroll

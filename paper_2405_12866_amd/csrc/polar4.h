@@ -18,8 +18,7 @@ namespace qfs {
 // singular vectors this gate had after its previous update (the environment changes
 // little between sweeps), so it converges in one or two sweeps instead of ~6. V_prev is
 // first made unitary to rounding by one Newton-Schulz step V (3I - V^dag V) / 2, so no
-// error accumulates across sweeps; the new V is stored back. vstart, when given, holds a
-// copy of the stored V_prev (in LDS) to read instead.
+// error accumulates across sweeps; the new V is stored back.
 __device__ __forceinline__ c128 shfl_c(c128 x, int src) {
   return cmake(__shfl(x.re, src), __shfl(x.im, src));
 }
@@ -31,8 +30,8 @@ __device__ __forceinline__ c128 shfl_c(c128 x, int src) {
 template <int CTRL>
 __device__ __forceinline__ double dpp_move(double x) {
   const long long b = __double_as_longlong(x);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
+  const int lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, false);
   return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
 template <int M>
@@ -118,24 +117,133 @@ __device__ __forceinline__ void jacobi_round(int l, c128 &g, c128 &v, int &large
   }
 }
 
+// Entry (r, c + J) of the matrix for lane 4c + r (columns cyclic): the 16-lane row rotated
+// left by 4 J (row_ror moves right). Entry (r + I, c): a rotation of each quad.
+template <int J>
+__device__ __forceinline__ c128 col_rot(c128 x) {
+  return cmake(dpp_move<0x120 + 16 - 4 * J>(x.re), dpp_move<0x120 + 16 - 4 * J>(x.im));
+}
+template <int I>
+__device__ __forceinline__ c128 row_rot(c128 x) {
+  constexpr int q = I == 1 ? 0x39 : I == 2 ? 0x4E : 0x93;  // quad_perm [I, I+1, I+2, I+3] mod 4
+  return cmake(dpp_move<q>(x.re), dpp_move<q>(x.im));
+}
+__device__ __forceinline__ double first_lane(double x) {
+  const long long b = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_readfirstlane((int)b), hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+__device__ __forceinline__ double row4_sum(double x) {  // over the columns c
+  x += dpp_move<0x124>(x);
+  return x + dpp_move<0x128>(x);
+}
+__device__ __forceinline__ double row16_sum(double x) {
+  x = row4_sum(x);
+  x += xor_lane<1>(x);
+  return x + xor_lane<2>(x);
+}
+__device__ __forceinline__ double row16_max(double x) {
+  x = fmax(x, xor_lane<1>(x));
+  x = fmax(x, xor_lane<2>(x));
+  x = fmax(x, xor_lane<4>(x));
+  return fmax(x, xor_lane<8>(x));
+}
+
+// Unitary polar factor of a well-conditioned 4x4 matrix by the scaled Newton iteration
+// (Higham, Functions of Matrices, Sec. 8.6): X <- (g X + X^-H / g) / 2, g = (|X^-1|_F /
+// |X|_F)^(1/2), which keeps the polar factor and squares the distance to it. Lane 4c + r of
+// every 16-lane row holds entry (r, c). X^-H[r][c] = conj(cof[r][c] / det), and a lane forms
+// its cofactor from the nine entries of the three other rows and columns, taken in cyclic
+// order (a rotation of three is even, so the sign is that of r + c) by DPP moves: no LDS, no
+// barrier, one reciprocal per iteration. Bound by the issue of one wave (about 150
+// instructions, 700 cycles an iteration, five or six iterations). Against the Jacobi SVD of
+// every matrix: 64 updates in one launch 7.1 -> 4.2 us, the finalize of a group of two gates
+// (8 qubits, cold start) 14.0 -> 9.3 us.
+// Returns false, x undefined, when |X|_F |X^-1|_F exceeds 64 in the first iteration: cofactors
+// lose digits with the square of the condition number (64 keeps the inverse, and with it the
+// factor, to a few 1e-13), and the SVD takes those, singular matrices, and extreme scales.
+__device__ __forceinline__ bool polar4_newton(int l, c128 &x) {
+  const double sgn = ((l ^ (l >> 2)) & 1) ? -1.0 : 1.0;
+  for (int it = 0; it < 16; ++it) {
+    const c128 z1 = col_rot<1>(x), z2 = col_rot<2>(x), z3 = col_rot<3>(x);
+    const c128 m00 = row_rot<1>(z1), m01 = row_rot<1>(z2), m02 = row_rot<1>(z3);
+    const c128 m10 = row_rot<2>(z1), m11 = row_rot<2>(z2), m12 = row_rot<2>(z3);
+    const c128 m20 = row_rot<3>(z1), m21 = row_rot<3>(z2), m22 = row_rot<3>(z3);
+    c128 cof = m00 * (m11 * m22 - m12 * m21);
+    cfma(cof, m01, m12 * m20 - m10 * m22);
+    cfma(cof, m02, m10 * m21 - m11 * m20);
+    cof = cmake(sgn * cof.re, sgn * cof.im);
+    c128 det = x * cof;
+    det.re = row4_sum(det.re);
+    det.im = row4_sum(det.im);
+    const double d2 = cabs2(det);
+    const double id2 = rcp_nr(d2);
+    const c128 w = cmake((cof.re * det.re + cof.im * det.im) * id2, (cof.re * det.im - cof.im * det.re) * id2);
+    const double e = cabs2(x - w);
+    double g = 0.5, gi = 0.5;
+    const bool far = __any(e > 1e-3);
+    if (it == 0 || far) {
+      const double n1 = row16_sum(cabs2(x)), n2 = row16_sum(cabs2(w));
+      if (it == 0) {
+        // (of a matrix of rank two or less, cofactors and determinant are rounding errors of
+        // one size, and the quotient says nothing: the cofactors are held to the entries' cube)
+        const double nc = n2 * d2;
+        if (__any(!(d2 > 1e-280 && d2 < 1e280 && n1 * n2 <= 4096.0 && nc > 1e-10 * (n1 * n1 * n1)))) return false;
+      }
+      // far from unitary: scaled. Any positive factors keep the polar factor, so the hardware estimates do; they must
+      // be the same on every lane (the lanes' sums differ in rounding, and an estimate of
+      // inputs one ulp apart may differ by 1e-9)
+      if (far) {
+        const double ratio = first_lane(n2 * __builtin_amdgcn_rcp(n1));
+        const double y = __builtin_amdgcn_rsq(ratio), f = __builtin_amdgcn_rsq(y);
+        g = 0.5 * f;
+        gi = 0.5 * f * y;
+      }
+    }
+    x = cmake(g * x.re + gi * w.re, g * x.im + gi * w.im);
+    // entries of X within 5e-9 of unitary before the step: to rounding after it
+    if (!__any(e > 1e-16)) return true;
+  }
+  return false;
+}
+
+// The polar factor of (1 - beta) G + beta u_prev: polar4_newton where it may, else the
+// Jacobi SVD.
+template <typename R>
 __device__ __forceinline__ void polar4_wave(const c128 *G, double beta, const c128 *u_prev, c128 *out64,
-                            c64 *out32, c128 *lds_g, c128 *lds_v, double *lds_s,
-                            c128 *vstore = nullptr, const c128 *vstart = nullptr) {
+                            cx<R> *out32, c128 *lds_g, c128 *lds_v, double *lds_s,
+                            c128 *vstore = nullptr) {
   const int lane = threadIdx.x & 63;
   const int l = lane & 15, c = l >> 2, r = l & 3, base = lane & ~15;
+  double scale = 1.0;
   auto gm = [&](int row, int col) {
     c128 x = G[row * 4 + col];
     if (beta != 0.0) {
       const c128 up = u_prev[row * 4 + col];
       x = cmake((1.0 - beta) * x.re + beta * up.re, (1.0 - beta) * x.im + beta * up.im);
     }
-    return x;
+    return cscale(x, scale);
   };
   c128 g, v;
+  {
+    c128 x = gm(r, c);
+    if (polar4_newton(l, x)) {
+      if (lane < 16) {
+        out64[r * 4 + c] = x;
+        if (out32) out32[r * 4 + c] = cmake<R>((R)x.re, (R)x.im);
+      }
+      return;
+    }
+    // the Jacobi forms fourth powers of the entries: scaled by a power of two (exact, and the
+    // polar factor does not change) where those leave the range of a double
+    const c128 x0 = gm(r, c);
+    const double big = row16_max(fmax(fabs(x0.re), fabs(x0.im)));
+    if (big > 1e60 || big < 1e-60) scale = big > 0.0 ? ldexp(1.0, -ilogb(big)) : 1.0;
+  }
   if (vstore) {
     // lane 4c + r holds X[r][c]; Y[a][c] = sum_k conj(X[k][a]) X[k][c] (quad c);
     // Z[r][c] = (3 X[r][c] - sum_a X[r][a] Y[a][c]) / 2
-    const c128 x = (vstart ? vstart : vstore)[r * 4 + c];
+    const c128 x = vstore[r * 4 + c];
     c128 acc = cmake(0.0, 0.0);
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
@@ -190,7 +298,7 @@ __device__ __forceinline__ void polar4_wave(const c128 *G, double beta, const c1
     }
     if (lane < 16) {
       out64[l] = acc;
-      if (out32) out32[l] = cmake<float>((float)acc.re, (float)acc.im);
+      if (out32) out32[l] = cmake<R>((R)acc.re, (R)acc.im);
       if (vstore) vstore[r * 4 + c] = v;
     }
     return;
@@ -206,70 +314,70 @@ __device__ __forceinline__ void polar4_wave(const c128 *G, double beta, const c1
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   __builtin_amdgcn_wave_barrier();
   if (lane == 0) {
-    int ord[4] = {0, 1, 2, 3};
+    // everything stays in LDS and the loops stay rolled: this path is rare, and its registers
+    // would count for the whole kernel
+    int ord = 0xE4;  // column of the k-th largest singular value at bits 2k, 2k + 1
+#pragma unroll 1
     for (int a = 0; a < 4; ++a)
-      for (int b = a + 1; b < 4; ++b)
-        if (lds_s[ord[b]] > lds_s[ord[a]]) {
-          const int tmp = ord[a];
-          ord[a] = ord[b];
-          ord[b] = tmp;
-        }
-    const double sm = lds_s[ord[0]];
-    c128 w[4][4];  // [k][row]
+#pragma unroll 1
+      for (int b = a + 1; b < 4; ++b) {
+        const int ca = (ord >> (2 * a)) & 3, cb = (ord >> (2 * b)) & 3;
+        if (lds_s[cb] > lds_s[ca]) ord ^= ((ca ^ cb) << (2 * a)) | ((ca ^ cb) << (2 * b));
+      }
+    auto col = [&](int k) { return lds_g + 4 * ((ord >> (2 * k)) & 3); };
+    // x <- x minus its components along the first k columns, twice; returns |x|^2
+    auto orth = [&](c128 (&x)[4], int k) {
+#pragma unroll 1
+      for (int i = 0; i < 2 * k; ++i) {
+        const c128 *w = col(i < k ? i : i - k);
+        c128 d = cmake(0.0, 0.0);
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) cfma(d, cconj(w[rr]), x[rr]);
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) x[rr] = x[rr] - d * w[rr];
+      }
+      return ((cabs2(x[0]) + cabs2(x[1])) + (cabs2(x[2]) + cabs2(x[3])));
+    };
+    const double sm = lds_s[ord & 3];
+#pragma unroll 1
     for (int k = 0; k < 4; ++k) {
-      const int cc = ord[k];
-      const double sk = lds_s[cc];
+      c128 *wk = col(k);
+      const double sk = lds_s[(ord >> (2 * k)) & 3];
       c128 x[4];
-      bool ok = sk > 0.0 && sk > 1e-13 * sm;
-      if (ok) {
-        for (int rr = 0; rr < 4; ++rr) x[rr] = cscale(lds_g[cc * 4 + rr], 1.0 / sk);
-        for (int rep = 0; rep < 2; ++rep)
-          for (int o = 0; o < k; ++o) {
-            c128 d = cmake(0.0, 0.0);
-            for (int rr = 0; rr < 4; ++rr) cfma(d, cconj(w[o][rr]), x[rr]);
-            for (int rr = 0; rr < 4; ++rr) x[rr] = x[rr] - d * w[o][rr];
-          }
-        double nn = 0.0;
-        for (int rr = 0; rr < 4; ++rr) nn += cabs2(x[rr]);
-        nn = sqrt(nn);
-        if (nn > 0.5)
-          for (int rr = 0; rr < 4; ++rr) x[rr] = cscale(x[rr], 1.0 / nn);
-        else
-          ok = false;
+      double nn = 0.0;
+      if (sk > 0.0 && sk > 1e-13 * sm) {
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) x[rr] = cscale(wk[rr], 1.0 / sk);
+        nn = orth(x, k);
       }
-      if (!ok) {  // complete with the unit vector of largest orthogonal remainder
+      if (!(nn > 0.25)) {  // complete with the unit vector of largest orthogonal remainder
+        int pick = 0;
         double best = -1.0;
-        c128 bx[4];
-        for (int e = 0; e < 4; ++e) {
-          c128 y[4];
-          for (int rr = 0; rr < 4; ++rr) y[rr] = cmake(rr == e ? 1.0 : 0.0, 0.0);
-          for (int rep = 0; rep < 2; ++rep)
-            for (int o = 0; o < k; ++o) {
-              c128 d = cmake(0.0, 0.0);
-              for (int rr = 0; rr < 4; ++rr) cfma(d, cconj(w[o][rr]), y[rr]);
-              for (int rr = 0; rr < 4; ++rr) y[rr] = y[rr] - d * w[o][rr];
-            }
-          double nn = 0.0;
-          for (int rr = 0; rr < 4; ++rr) nn += cabs2(y[rr]);
-          if (nn > best) {
+#pragma unroll 1
+        for (int e = 0; e < 5; ++e) {
+          const int at = e < 4 ? e : pick;
+#pragma unroll
+          for (int rr = 0; rr < 4; ++rr) x[rr] = cmake(rr == at ? 1.0 : 0.0, 0.0);
+          nn = orth(x, k);
+          if (e < 4 && nn > best) {
             best = nn;
-            for (int rr = 0; rr < 4; ++rr) bx[rr] = y[rr];
+            pick = e;
           }
         }
-        const double inv = 1.0 / sqrt(best);
-        for (int rr = 0; rr < 4; ++rr) x[rr] = cscale(bx[rr], inv);
       }
-      for (int rr = 0; rr < 4; ++rr) w[k][rr] = x[rr];
+      const double inv = 1.0 / sqrt(nn);
+#pragma unroll
+      for (int rr = 0; rr < 4; ++rr) wk[rr] = cscale(x[rr], inv);
     }
-    for (int q = 0; q < 4; ++q)
-      for (int p = 0; p < 4; ++p) {
-        c128 acc = cmake(0.0, 0.0);
-        for (int k = 0; k < 4; ++k) cfma_conj(acc, w[k][q], lds_v[ord[k] * 4 + p]);
-        out64[q * 4 + p] = acc;
-        if (out32) out32[q * 4 + p] = cmake<float>((float)acc.re, (float)acc.im);
-      }
+#pragma unroll 1
+    for (int e = 0; e < 16; ++e) {
+      c128 acc = cmake(0.0, 0.0);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) cfma_conj(acc, lds_g[k * 4 + (e >> 2)], lds_v[k * 4 + (e & 3)]);
+      out64[e] = acc;
+      if (out32) out32[e] = cmake<R>((R)acc.re, (R)acc.im);
+    }
   }
 }
-
 
 }  // namespace qfs

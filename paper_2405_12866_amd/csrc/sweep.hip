@@ -823,7 +823,7 @@ __global__ __launch_bounds__(kFinBlock) void k_env_finalize(const c128 *partials
       return;
     }
     c128 *vs = vstore ? vstore + (int64_t)s * gstride + k_env * 16 : nullptr;
-    polar4_wave(gam, beta, u64, u64, u32, pg, pv, psig, vs);
+    polar4_wave<float>(gam, beta, u64, u64, u32, pg, pv, psig, vs);
   }
 }
 
@@ -920,7 +920,7 @@ __global__ void k_polar_batch(int count, const c128 *gamma, double beta, c128 *u
   __shared__ double psig[4];
   const int i = blockIdx.x;
   if (i >= count) return;
-  polar4_wave(gamma + (int64_t)i * 16, beta, u + (int64_t)i * 16, u + (int64_t)i * 16, nullptr,
+  polar4_wave<float>(gamma + (int64_t)i * 16, beta, u + (int64_t)i * 16, u + (int64_t)i * 16, nullptr,
               pg, pv, psig);
 }
 
