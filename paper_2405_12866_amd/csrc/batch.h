@@ -37,7 +37,6 @@ struct BProb {
   const c128 *U;          // DENSE target
   const c128 *s_psi, *s_phi;  // SAMPLES target rows
   c128 *psi, *phi, *psiv, *phiv;  // FP64 masters, sample-major [M][N]
-  c128 *coef;             // Gram-Schmidt scratch [mcap]
   c128 *g64;              // [S][L][16]
   c128 *vst;              // [S][L][16] Jacobi warm start
   int32_t done_sweep;     // smallest sweep count at which a start succeeded

@@ -149,7 +149,8 @@ int qfs::batch_instantiate(int32_t P, const qfs_template *tmpl, const qfs_target
 
   // ---------------------------------------------------------------- validation + sizes
   std::vector<BProb> hp(P);
-  std::vector<size_t> off_psi(P), off_psiv(P), off_coef(P), off_g(P), off_pairs(P), off_tpairs(P),
+  std::vector<int> mvcaps(P);
+  std::vector<size_t> off_psi(P), off_psiv(P), off_g(P), off_pairs(P), off_tpairs(P),
       off_kinds(P);
   size_t c128s = 0, ints = 0;
   for (int i = 0; i < P; ++i) {
@@ -231,8 +232,7 @@ int qfs::batch_instantiate(int32_t P, const qfs_template *tmpl, const qfs_target
     c128s += 2 * (size_t)mcap * N;
     off_psiv[i] = c128s;
     c128s += 2 * (size_t)std::max(mvcap, 1) * N;
-    off_coef[i] = c128s;
-    c128s += (size_t)std::max(mcap, mvcap) + 1;
+    mvcaps[i] = std::max(mvcap, 1);
     off_g[i] = c128s;
     c128s += 2 * (size_t)S * t.n_gates * 16;
     off_pairs[i] = ints;
@@ -272,12 +272,10 @@ int qfs::batch_instantiate(int32_t P, const qfs_template *tmpl, const qfs_target
   for (int i = 0; i < P; ++i) {
     BProb &d = hp[i];
     const int N = 1 << d.n;
-    const int mvcap = (int)((off_coef[i] - off_psiv[i]) / (2 * (size_t)N));
     d.psi = base + off_psi[i];
     d.phi = d.psi + (size_t)d.mcap * N;
     d.psiv = base + off_psiv[i];
-    d.phiv = d.psiv + (size_t)mvcap * N;
-    d.coef = base + off_coef[i];
+    d.phiv = d.psiv + (size_t)mvcaps[i] * N;
     d.g64 = base + off_g[i];
     d.vst = d.g64 + (size_t)S * d.L * 16;
     std::memcpy(hints.data() + off_pairs[i], tmpl[i].pairs, sizeof(int32_t) * 2 * d.L);
