@@ -57,14 +57,14 @@ const char *qfs_strerror(int code);
 const char *qfs_last_error_detail(void);
 /* Library version string. */
 const char *qfs_version(void);
-/* Device memory kept between calls. When a call of qfs_instantiate (and of the entry
- * points built on it: qfs_instantiate_samples, the learned single-problem entry) ends, the
- * library keeps its device buffers, up to an eighth of the device's memory, and reuses
- * them in later calls that need buffers of the same sizes, instead of freeing and
- * allocating them again. An allocation that fails frees the kept buffers first, and the
+/* Device memory kept between calls. When a call ends (the instantiation entries, single,
+ * batched and qudit, and the step entries that need working buffers), the library keeps its
+ * device buffers, up to an eighth of the device's memory in all (the oldest are freed beyond
+ * that), and reuses them in later calls that need buffers of like sizes, instead of freeing
+ * and allocating them again. An allocation that fails frees the kept buffers first, and the
  * free-memory budget of a call counts them as free. This frees the buffers kept for the
  * current device and stores their total size in *bytes_freed (may be null). Blocks are
- * kept only once the device has finished with them, so it may be called at any time, from
+ * kept only once the work that used them has ended, so it may be called at any time, from
  * any thread. Returns QFS_OK or QFS_EDEVICE. */
 int qfs_release_device_cache(size_t *bytes_freed);
 

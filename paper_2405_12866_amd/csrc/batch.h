@@ -53,6 +53,12 @@ struct BJob {
   double work;  // sum over this job's sweeps of (M + Mv) 2^n L
 };
 
+struct BMove {  // a problem's returned gates to the caller's tensor
+  const c128 *src;
+  c128 *dst;
+  int32_t count;
+};
+
 struct BParams {
   double dist_tol, diff_tol_r, overtrain_ratio, beta, refine_below;
   int32_t plateau_window, min_iter;
@@ -94,6 +100,7 @@ int launch_batch_setup(BProb *probs_dev, const int32_t *todo, int ntodo, const i
                        hipStream_t s);
 int launch_batch_gates(BProb *probs_dev, const int32_t *prob_of, const int32_t *first_gate,
                        int total, hipStream_t s);
+int launch_batch_move(const BMove *moves, int count, hipStream_t s);
 int launch_batch_sweep(const BatchArgs &a, bool fp64, int threads, int grid, size_t lds,
                        hipStream_t s);
 

@@ -608,9 +608,21 @@ __global__ void k_batch_gates(BProb *probs, const int32_t *prob_of, const int32_
     for (int c = 0; c < 4; ++c) u[r * 4 + c] = q[c][r];
 }
 
+__global__ void k_batch_move(const BMove *moves) {
+  const BMove m = moves[blockIdx.x];
+  for (int e = threadIdx.x; e < m.count; e += blockDim.x) m.dst[e] = m.src[e];
+}
+
 }  // namespace
 
 // ------------------------------------------------------------------ launchers
+int launch_batch_move(const BMove *moves, int count, hipStream_t s) {
+  if (count <= 0) return QFS_OK;
+  hipLaunchKernelGGL(k_batch_move, dim3(count), dim3(256), 0, s, moves);
+  QFS_HIP(hipGetLastError());
+  return QFS_OK;
+}
+
 int launch_batch_setup(BProb *probs_dev, const int32_t *todo, int ntodo, const int32_t *m0s,
                        hipStream_t s) {
   if (ntodo <= 0) return QFS_OK;

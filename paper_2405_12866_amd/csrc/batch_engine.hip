@@ -120,6 +120,7 @@ int qfs::batch_instantiate(int32_t P, const qfs_template *tmpl, const qfs_target
                            const qfs_params *params, qfs_c128 *const *gates_out, qfs_result *res,
                            const BatchOpts &opts) {
   const double t0 = bnow();
+  BufferScope scope;
   if (P < 1 || !tmpl || !targets || !params || !gates_out || !res) {
     set_error_detail("batch: null argument or P < 1");
     return QFS_EINVAL;
@@ -254,7 +255,7 @@ int qfs::batch_instantiate(int32_t P, const qfs_template *tmpl, const qfs_target
   int dev = 0;
   QFS_HIP(hipMemGetInfo(&fr, &tot));
   QFS_HIP(hipGetDevice(&dev));
-  // (blocks the single-problem engine caches are freed on demand by DevBuf::alloc)
+  // (cached blocks of earlier calls are freed on demand by an allocation that fails)
   const size_t budget =
       p.device_mem_budget ? p.device_mem_budget : (size_t)(0.9 * (double)(fr + device_cache_held(dev)));
   const size_t njobs_all = (size_t)P * S;
@@ -677,6 +678,9 @@ int qfs::batch_instantiate(int32_t P, const qfs_template *tmpl, const qfs_target
 
   // ---------------------------------------------------------------- results
   const double secs = bnow() - t0;
+  std::vector<BMove> moves;
+  DevBuf dmoves;
+  moves.reserve(P);
   for (int i = 0; i < P; ++i) {
     const BJob *js = jobs.data() + (size_t)i * S;
     int w = winner[i];
@@ -706,11 +710,15 @@ int qfs::batch_instantiate(int32_t P, const qfs_template *tmpl, const qfs_target
     }
     r.sweep_seconds = kernel_seconds;
     if (gates_out[i])
-      QFS_HIP(hipMemcpyAsync(gates_out[i], hp[i].g64 + (size_t)w * hp[i].L * 16,
-                             sizeof(c128) * 16 * hp[i].L, hipMemcpyDeviceToDevice, st));
+      moves.push_back({hp[i].g64 + (size_t)w * hp[i].L * 16, reinterpret_cast<c128 *>(gates_out[i]), 16 * hp[i].L});
   }
-  QFS_HIP(hipStreamSynchronize(st));
-  return QFS_OK;
+  if (!moves.empty()) {
+    // every problem's gates in one launch (a copy each cost more than a short run's sweeps)
+    QFS_TRY(dmoves.alloc(sizeof(BMove) * moves.size()));
+    QFS_HIP(hipMemcpyAsync(dmoves.ptr, moves.data(), sizeof(BMove) * moves.size(), hipMemcpyHostToDevice, st));
+    QFS_TRY(launch_batch_move(dmoves.as<BMove>(), (int)moves.size(), st));
+  }
+  return scope.done(st);
 }
 
 extern "C" int qfs_instantiate_batch(int32_t P, const qfs_template *tmpl, const qfs_target *targets,

@@ -8,6 +8,7 @@
 #include <chrono>
 #include <cmath>
 #include <cstring>
+#include <list>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -45,15 +46,20 @@ int ensure_dynamic_lds(const void *fn, size_t bytes, size_t *have) {
   return QFS_OK;
 }
 
-// Device blocks kept between calls of the engine, by device and exact size. hipMalloc of
-// the large working sets and hipFree (which drains the device) otherwise cost several
-// hundred microseconds each in every call, during which the device idles. The cache holds
-// at most an eighth of the device's memory; blocks beyond that are freed.
+// Device blocks kept between calls, by device and exact size, in the order they came back.
+// hipMalloc of the large working sets and hipFree (which drains the device) otherwise cost
+// several hundred microseconds each in every call, during which the device idles. The cache
+// holds at most an eighth of the device's memory; the oldest blocks are freed beyond that.
 namespace {
+struct CachedBlock {
+  int dev;
+  size_t bytes;
+  void *ptr;
+};
 struct BlockCache {
   std::mutex mu;
-  std::multimap<std::pair<int, size_t>, void *> blocks;
-  std::map<int, size_t> held;
+  std::list<CachedBlock> blocks;
+  std::map<int, size_t> held, cap;
 };
 BlockCache &block_cache() {
   static BlockCache *c = new BlockCache;  // never destroyed: no HIP calls at process exit
@@ -73,12 +79,14 @@ bool cache_poison() {
 void *device_cache_take(int dev, size_t bytes) {
   BlockCache &c = block_cache();
   std::lock_guard<std::mutex> lk(c.mu);
-  auto it = c.blocks.find({dev, bytes});
-  if (it == c.blocks.end()) return nullptr;
-  void *p = it->second;
-  c.blocks.erase(it);
-  c.held[dev] -= bytes;
-  return p;
+  for (auto it = c.blocks.rbegin(); it != c.blocks.rend(); ++it)
+    if (it->dev == dev && it->bytes == bytes) {
+      void *p = it->ptr;
+      c.blocks.erase(std::next(it).base());
+      c.held[dev] -= bytes;
+      return p;
+    }
+  return nullptr;
 }
 
 size_t device_cache_held(int dev) {
@@ -92,13 +100,113 @@ size_t device_cache_trim(int dev) {
   BlockCache &c = block_cache();
   std::lock_guard<std::mutex> lk(c.mu);
   size_t freed = 0;
-  for (auto it = c.blocks.lower_bound({dev, 0}); it != c.blocks.end() && it->first.first == dev;) {
-    (void)hipFree(it->second);
-    freed += it->first.second;
+  for (auto it = c.blocks.begin(); it != c.blocks.end();) {
+    if (it->dev != dev) {
+      ++it;
+      continue;
+    }
+    (void)hipFree(it->ptr);
+    freed += it->bytes;
     it = c.blocks.erase(it);
   }
   c.held[dev] -= freed;
   return freed;
+}
+
+// Takes idle blocks (no queued work uses them) of device dev.
+static void device_cache_put(int dev, std::vector<std::pair<void *, size_t>> &blks) {
+  BlockCache &c = block_cache();
+  std::lock_guard<std::mutex> lk(c.mu);
+  size_t &held = c.held[dev], &cap = c.cap[dev];
+  if (cap == 0) {
+    size_t fr = 0, tot = 0;
+    if (hipMemGetInfo(&fr, &tot) == hipSuccess)
+      cap = tot / 8;
+    else
+      (void)hipGetLastError();
+  }
+  for (auto &b : blks) {
+    if (b.second > cap) {
+      (void)hipFree(b.first);
+      continue;
+    }
+    for (auto it = c.blocks.begin(); held + b.second > cap && it != c.blocks.end();) {
+      if (it->dev != dev) {
+        ++it;
+        continue;
+      }
+      (void)hipFree(it->ptr);
+      held -= it->bytes;
+      it = c.blocks.erase(it);
+    }
+    // (waited for: the next user may be on a stream that the null stream does not order)
+    if (cache_poison() && (hipMemset(b.first, 0xff, b.second) != hipSuccess ||
+                           hipStreamSynchronize(nullptr) != hipSuccess))
+      (void)hipGetLastError();
+    c.blocks.push_back({dev, b.second, b.first});
+    held += b.second;
+  }
+  blks.clear();
+}
+
+// ------------------------------------------------------------------ per-call buffers
+static thread_local BufferScope *t_scope = nullptr;
+
+BufferScope *BufferScope::current() { return t_scope; }
+BufferScope::BufferScope() : outer_(t_scope) {
+  if (hipGetDevice(&dev_) != hipSuccess) (void)hipGetLastError();
+  t_scope = this;
+}
+BufferScope::~BufferScope() {
+  t_scope = outer_;
+  if (kept_.empty()) return;
+  if (idle_ || hipDeviceSynchronize() == hipSuccess) {
+    device_cache_put(dev_, kept_);
+  } else {
+    (void)hipGetLastError();
+    for (auto &b : kept_) (void)hipFree(b.first);
+  }
+}
+int BufferScope::done(hipStream_t s) {
+  QFS_HIP(hipStreamSynchronize(s));
+  idle_ = true;
+  return QFS_OK;
+}
+void BufferScope::give_back(void *self, void *p, size_t bytes) {
+  static_cast<BufferScope *>(self)->kept_.emplace_back(p, bytes);
+}
+int BufferScope::alloc(DevBuf &b, size_t bytes) {
+  // size classes, so that calls of like sizes find each other's blocks: powers of two up to
+  // 1 MiB, eighths of one beyond (at most an eighth more than asked for)
+  size_t cls = 256;
+  while (cls < bytes && cls < (size_t(1) << 20)) cls <<= 1;
+  if (cls < bytes) {
+    while (cls * 2 <= bytes) cls <<= 1;
+    cls = (bytes + cls / 8 - 1) / (cls / 8) * (cls / 8);
+  }
+  void *p = device_cache_take(dev_, cls);
+  if (!p) {
+    hipError_t e = hipMalloc(&p, cls);
+    if (e == hipErrorOutOfMemory) {
+      (void)hipGetLastError();
+      QFS_HIP(hipDeviceSynchronize());  // the blocks this call has released are idle then
+      for (auto &k : kept_) (void)hipFree(k.first);
+      kept_.clear();
+      (void)device_cache_trim(dev_);
+      cls = bytes;
+      e = hipMalloc(&p, cls);
+    }
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      set_error_detail(std::string("hipMalloc(") + std::to_string(bytes) + "): " + hipGetErrorString(e));
+      return e == hipErrorOutOfMemory ? QFS_ENOMEM : QFS_EDEVICE;
+    }
+  }
+  b.ptr = p;
+  b.bytes = cls;
+  b.give_back = &BufferScope::give_back;
+  b.owner = this;
+  return QFS_OK;
 }
 
 // Pinned host buffers for the per-sweep costs, kept for later calls (hipHostMalloc and
@@ -131,27 +239,6 @@ static void *pinned_take(size_t bytes) {
 static void pinned_put(void *p, size_t bytes) {
   std::lock_guard<std::mutex> lk(g_pin_mu);
   g_pins.emplace(bytes, p);
-}
-
-// Takes idle blocks (the device has drained since their last use) of device dev.
-static void device_cache_put(int dev, std::vector<std::pair<void *, size_t>> &blks) {
-  size_t fr = 0, tot = 0;
-  if (hipMemGetInfo(&fr, &tot) != hipSuccess) {
-    (void)hipGetLastError();
-    tot = 0;
-  }
-  BlockCache &c = block_cache();
-  std::lock_guard<std::mutex> lk(c.mu);
-  for (auto &b : blks) {
-    if (c.held[dev] + b.second > tot / 8) {
-      (void)hipFree(b.first);
-      continue;
-    }
-    if (cache_poison() && hipMemset(b.first, 0xff, b.second) != hipSuccess) (void)hipGetLastError();
-    c.blocks.emplace(std::make_pair(dev, b.second), b.first);
-    c.held[dev] += b.second;
-  }
-  blks.clear();
 }
 
 namespace {
@@ -1836,16 +1923,16 @@ int qfs_draw_states(int32_t n, int32_t M, uint64_t seed, uint32_t role, uint32_t
                     qfs_c128 *out, void *hip_stream) {
   if (n < 1 || n > 24 || M < 1 || (int64_t)M > (int64_t(1) << n) || !out) return QFS_EINVAL;
   hipStream_t s = as_stream(hip_stream);
+  BufferScope scope;
   const int64_t N = int64_t(1) << n, ld = master_ld(M);
   DevBuf A, W;
   QFS_TRY(A.alloc(sizeof(c128) * N * ld));
-  QFS_TRY(launch_zero(A.ptr, A.bytes, s));
+  QFS_TRY(launch_zero(A.ptr, sizeof(c128) * N * ld, s));
   QFS_TRY(launch_ginibre(N, 0, M, ld, seed, role, stream, A.as<c128>(), s));
   QFS_TRY(W.alloc(work_bytes_orth(N, M)));
   QFS_TRY(orthonormalize_columns(N, ld, 0, M, A.as<c128>(), W.ptr, s));
   QFS_TRY(launch_from_internal<double>(n, M, ceil_log2(ld), A.as<c128>(), reinterpret_cast<c128 *>(out), s));
-  QFS_HIP(hipStreamSynchronize(s));
-  return QFS_OK;
+  return scope.done(s);
 }
 
 int qfs_haar_gates(uint64_t seed, int32_t starts, int32_t L, qfs_c128 *out, void *hip_stream) {
@@ -1862,6 +1949,7 @@ int qfs_apply_gates(int32_t n, int32_t M, qfs_c128 *states, int32_t L, const int
   QFS_TRY(validate_template(&t));
   if (M < 1 || !states || !gates) return QFS_EINVAL;
   hipStream_t s = as_stream(hip_stream);
+  BufferScope scope;
   const Geometry g = api_geometry(n, M);
   DevBuf A, slot;
   QFS_TRY(A.alloc(sizeof(c128) * g.elems()));
@@ -1875,14 +1963,14 @@ int qfs_apply_gates(int32_t n, int32_t M, qfs_c128 *states, int32_t L, const int
                                  slot.as<int32_t>(), 1, s));
   }
   QFS_TRY(launch_from_internal<double>(n, M, g.logC, A.as<c128>(), reinterpret_cast<c128 *>(states), s));
-  QFS_HIP(hipStreamSynchronize(s));
-  return QFS_OK;
+  return scope.done(s);
 }
 
 int qfs_dense_apply(int32_t n, int32_t M, const qfs_c128 *U, const qfs_c128 *psi, qfs_c128 *out,
                     void *hip_stream) {
   if (n < 1 || n > 16 || M < 1 || !U || !psi || !out) return QFS_EINVAL;
   hipStream_t s = as_stream(hip_stream);
+  BufferScope scope;
   const int64_t N = int64_t(1) << n, ld = master_ld(M);
   DevBuf A, B;
   QFS_TRY(A.alloc(sizeof(c128) * N * ld));
@@ -1891,8 +1979,7 @@ int qfs_dense_apply(int32_t n, int32_t M, const qfs_c128 *U, const qfs_c128 *psi
   QFS_TRY(launch_zgemm(false, (int)N, (int)ld, (int)N, cmake(1.0, 0.0), reinterpret_cast<const c128 *>(U),
                        (int)N, A.as<c128>(), (int)ld, cmake(0.0, 0.0), B.as<c128>(), (int)ld, s));
   QFS_TRY(launch_from_internal<double>(n, M, ceil_log2(ld), B.as<c128>(), reinterpret_cast<c128 *>(out), s));
-  QFS_HIP(hipStreamSynchronize(s));
-  return QFS_OK;
+  return scope.done(s);
 }
 
 int qfs_environment(int32_t n, int32_t M, const qfs_c128 *a, const qfs_c128 *b, int32_t qa,
@@ -1902,6 +1989,7 @@ int qfs_environment(int32_t n, int32_t M, const qfs_c128 *a, const qfs_c128 *b, 
   QFS_TRY(validate_template(&t));
   if (M < 1 || !a || !b || !gamma) return QFS_EINVAL;
   hipStream_t s = as_stream(hip_stream);
+  BufferScope scope;
   const Geometry g = api_geometry(n, M);
   DevBuf A, B, slot, part;
   QFS_TRY(A.alloc(sizeof(c128) * g.elems()));
@@ -1917,8 +2005,7 @@ int qfs_environment(int32_t n, int32_t M, const qfs_c128 *a, const qfs_c128 *b, 
                                   slot.as<int32_t>(), 1, part.as<c128>(), &P, s));
   QFS_TRY(launch_env_finalize(P, part.as<c128>(), slot.as<int32_t>(), 1, reinterpret_cast<c128 *>(gamma),
                               false, 0.0, nullptr, nullptr, 0, 0, nullptr, QFS_GATE_2Q, s));
-  QFS_HIP(hipStreamSynchronize(s));
-  return QFS_OK;
+  return scope.done(s);
 }
 
 int qfs_polar_update(int32_t count, const qfs_c128 *gamma, double beta, qfs_c128 *u,
@@ -1935,6 +2022,7 @@ int qfs_state_distance(int32_t n, int32_t M, const qfs_c128 *x, const qfs_c128 *
                        void *hip_stream) {
   if (n < 2 || n > 24 || M < 1 || !x || !y || !result) return QFS_EINVAL;
   hipStream_t s = as_stream(hip_stream);
+  BufferScope scope;
   const Geometry g = api_geometry(n, M);
   DevBuf A, B, slot, part, out;
   QFS_TRY(A.alloc(sizeof(c128) * g.elems()));
@@ -1951,8 +2039,7 @@ int qfs_state_distance(int32_t n, int32_t M, const qfs_c128 *x, const qfs_c128 *
                                     part.as<double>(), &P, s));
   QFS_TRY(launch_dist_finalize(P, part.as<double>(), slot.as<int32_t>(), 1, M, out.as<double>(), s));
   QFS_HIP(hipMemcpyAsync(result, out.ptr, sizeof(double), hipMemcpyDeviceToHost, s));
-  QFS_HIP(hipStreamSynchronize(s));
-  return QFS_OK;
+  return scope.done(s);
 }
 
 int qfs_sweep(int32_t n, int32_t L, const int32_t *pairs, const int32_t *kinds, int32_t M,
@@ -1973,6 +2060,7 @@ int qfs_sweep(int32_t n, int32_t L, const int32_t *pairs, const int32_t *kinds, 
       (backward_mode != QFS_BWD_GROUPED && backward_mode != QFS_BWD_PER_GATE))
     return QFS_EINVAL;
   hipStream_t s = as_stream(hip_stream);
+  BufferScope scope;
   const bool f32 = precision == QFS_PREC_MIXED;
   const size_t rb = f32 ? sizeof(float) : sizeof(double), cb = 2 * rb;
   const size_t lds = lds_max_bytes();
@@ -1984,12 +2072,6 @@ int qfs_sweep(int32_t n, int32_t L, const int32_t *pairs, const int32_t *kinds, 
   c.L = L;
   c.pairs_host = pairs;
   c.kinds = kinds;
-  DevBuf kdev;
-  if (kinds) {
-    QFS_TRY(kdev.alloc(sizeof(int32_t) * L));
-    QFS_HIP(hipMemcpyAsync(kdev.ptr, kinds, sizeof(int32_t) * L, hipMemcpyHostToDevice, s));
-    c.kinds_dev = kdev.as<int32_t>();
-  }
   c.g = Geometry{n, 1 << n, logC, (M + C - 1) / C, M};
   c.gv = Geometry{n, 1 << n, logC, 1, 0};
   c.fused = fused;
@@ -1999,21 +2081,24 @@ int qfs_sweep(int32_t n, int32_t L, const int32_t *pairs, const int32_t *kinds, 
   c.timer = &timer;
   c.stream = s;
   const size_t set = (size_t)c.g.elems() * cb;
-  DevBuf ps, ph, Bl, As, g32, slots, part, dpart, costs, pdev;
+  DevBuf ps, ph, Bl, As, g32, part, dpart, costs, ints;
   QFS_TRY(ps.alloc(set));
   QFS_TRY(ph.alloc(set));
   QFS_TRY(Bl.alloc(set * (size_t)std::max(L - 1, 1) * starts));
   QFS_TRY(As.alloc(set * starts));
   QFS_TRY(g32.alloc(sizeof(c64) * 16 * (size_t)L * starts));
-  QFS_TRY(slots.alloc(sizeof(int32_t) * starts));
   QFS_TRY(part.alloc(sizeof(c128) * 16 * kPcap * (size_t)starts));
   QFS_TRY(dpart.alloc(sizeof(double) * 2 * kPcap * (size_t)starts));
   QFS_TRY(costs.alloc(sizeof(double) * 3 * starts));
-  QFS_TRY(pdev.alloc(sizeof(int32_t) * 2 * L));
-  QFS_HIP(hipMemcpyAsync(pdev.ptr, pairs, sizeof(int32_t) * 2 * L, hipMemcpyHostToDevice, s));
-  std::vector<int32_t> sl(starts);
-  for (int i = 0; i < starts; ++i) sl[i] = i;
-  QFS_HIP(hipMemcpyAsync(slots.ptr, sl.data(), sizeof(int32_t) * starts, hipMemcpyHostToDevice, s));
+  // the slots, pairs, kinds and plans go to the device in one copy
+  std::vector<int32_t> ih(starts);
+  for (int i = 0; i < starts; ++i) ih[i] = i;
+  auto put = [&](const int32_t *src, size_t count) {
+    const size_t at = ih.size();
+    ih.insert(ih.end(), src, src + count);
+    return at;
+  };
+  const size_t at_pairs = put(pairs, 2 * (size_t)L), at_kinds = kinds ? put(kinds, L) : 0;
   if (f32) {
     QFS_TRY(launch_to_internal<float>(n, M, logC, c.g.nch, reinterpret_cast<const c128 *>(psi), ps.as<c64>(), s));
     QFS_TRY(launch_to_internal<float>(n, M, logC, c.g.nch, reinterpret_cast<const c128 *>(phi), ph.as<c64>(), s));
@@ -2022,8 +2107,6 @@ int qfs_sweep(int32_t n, int32_t L, const int32_t *pairs, const int32_t *kinds, 
     QFS_TRY(launch_to_internal<double>(n, M, logC, c.g.nch, reinterpret_cast<const c128 *>(psi), ps.as<c128>(), s));
     QFS_TRY(launch_to_internal<double>(n, M, logC, c.g.nch, reinterpret_cast<const c128 *>(phi), ph.as<c128>(), s));
   }
-  c.pairs_dev = pdev.as<int32_t>();
-  c.slots = slots.as<int32_t>();
   c.nslots = starts;
   c.g64 = reinterpret_cast<c128 *>(gates);
   c.g32 = g32.as<c64>();
@@ -2037,7 +2120,8 @@ int qfs_sweep(int32_t n, int32_t L, const int32_t *pairs, const int32_t *kinds, 
   c.costs = costs.as<double>();
   std::vector<GateGroup> groups;
   std::vector<int32_t> need, fplan_h, fgslot_h;
-  DevBuf gpart, bneed, vopb, fplan_d, fgslot_d;
+  DevBuf gpart, vopb;
+  size_t at_need = 0, at_plan = 0, at_gslot = 0;
   c.grouped = backward_mode == QFS_BWD_GROUPED && group_path_supported(c.g, rb);
   if (c.grouped) {
     groups = plan_gate_groups(L, pairs, kinds);
@@ -2048,10 +2132,8 @@ int qfs_sweep(int32_t n, int32_t L, const int32_t *pairs, const int32_t *kinds, 
     QFS_TRY(gpart.alloc(sizeof(c128) * 256 * (size_t)c.gpstride * starts));
     QFS_TRY(vopb.alloc(sizeof(c128) * 256 * (size_t)starts));
     c.vop = vopb.as<c128>();
-    QFS_TRY(bneed.alloc(sizeof(int32_t) * L));
-    QFS_HIP(hipMemcpyAsync(bneed.ptr, need.data(), sizeof(int32_t) * L, hipMemcpyHostToDevice, s));
+    at_need = put(need.data(), need.size());
     c.groups = &groups;
-    c.bneed_dev = bneed.as<int32_t>();
     c.gpartials = gpart.as<c128>();
     // how the forward pass applies each gate; a constant gate counts as a CNOT only if it
     // is one in every start's gates
@@ -2068,16 +2150,22 @@ int qfs_sweep(int32_t n, int32_t L, const int32_t *pairs, const int32_t *kinds, 
       fmode = forward_gate_modes(L, kinds, gh.empty() ? nullptr : gh.data(), starts);
     }
     if (f32 && fused && build_forward_plan(c.g, L, pairs, groups, need.data(), fmode.data(), fplan_h, fgslot_h) == QFS_OK) {
-      QFS_TRY(fplan_d.alloc(sizeof(int32_t) * fplan_h.size()));
-      QFS_TRY(fgslot_d.alloc(sizeof(int32_t) * fgslot_h.size()));
-      QFS_HIP(hipMemcpyAsync(fplan_d.ptr, fplan_h.data(), sizeof(int32_t) * fplan_h.size(), hipMemcpyHostToDevice, s));
-      QFS_HIP(hipMemcpyAsync(fgslot_d.ptr, fgslot_h.data(), sizeof(int32_t) * fgslot_h.size(),
-                             hipMemcpyHostToDevice, s));
-      c.fplan = fplan_d.as<int32_t>();
-      c.fgslot = fgslot_d.as<int32_t>();
+      at_plan = put(fplan_h.data(), fplan_h.size());
+      at_gslot = put(fgslot_h.data(), fgslot_h.size());
       c.fngroups = (int)groups.size();
       c.fforms = std::any_of(fmode.begin(), fmode.end(), [](int32_t m) { return m != kFwdDense; });
     }
+  }
+  QFS_TRY(ints.alloc(sizeof(int32_t) * ih.size()));
+  QFS_HIP(hipMemcpyAsync(ints.ptr, ih.data(), sizeof(int32_t) * ih.size(), hipMemcpyHostToDevice, s));
+  const int32_t *idev = ints.as<int32_t>();
+  c.slots = idev;
+  c.pairs_dev = idev + at_pairs;
+  if (kinds) c.kinds_dev = idev + at_kinds;
+  if (at_need) c.bneed_dev = idev + at_need;
+  if (at_plan) {
+    c.fplan = idev + at_plan;
+    c.fgslot = idev + at_gslot;
   }
   if (f32) {
     QFS_TRY(sweep_forward<float>(c, false));
@@ -2087,8 +2175,7 @@ int qfs_sweep(int32_t n, int32_t L, const int32_t *pairs, const int32_t *kinds, 
     QFS_TRY(sweep_backward<double>(c));
   }
   QFS_HIP(hipMemcpyAsync(c_train, costs.ptr, sizeof(double) * starts, hipMemcpyDeviceToHost, s));
-  QFS_HIP(hipStreamSynchronize(s));
-  return QFS_OK;
+  return scope.done(s);
 }
 
 }  // extern "C"

@@ -108,12 +108,39 @@ int pool_stream(int index, hipStream_t *out);
   } while (0)
 
 // ------------------------------------------------------------------ device buffers
-// Blocks that calls of the single-problem engine give back when they end, kept for the
-// next call of the same size instead of hipFree (engine.hip). Every block in the cache is
-// idle: a call gives its blocks back only after the device has drained.
+// Blocks that finished calls give back, kept for later calls instead of hipFree (engine.hip;
+// bounded, the oldest freed first). Every block in the cache is idle: a call gives its blocks
+// back only after the work that used them has ended.
 void *device_cache_take(int dev, size_t bytes);
 size_t device_cache_held(int dev);
 size_t device_cache_trim(int dev);  // frees the device's cached blocks; returns the bytes freed
+
+struct DevBuf;
+
+// While one is open on a thread, DevBuf::alloc on that thread takes its blocks from the cache,
+// and the blocks released go back to it when the scope ends. hipMalloc and hipFree of the
+// working sets cost far more than the kernels of a step entry (an 11-qubit FP64 sweep of 5
+// starts: 14.8 ms a call with them, 0.69 without). A block released inside a call is not handed
+// out again before its end, so kernels still queued on any of the call's streams keep it.
+// done(): waits for the call's stream, after which its blocks are idle; a scope that ends
+// without it (an error path) waits for the whole device.
+class BufferScope {
+ public:
+  BufferScope();
+  ~BufferScope();
+  BufferScope(const BufferScope &) = delete;
+  BufferScope &operator=(const BufferScope &) = delete;
+  int done(hipStream_t s);
+  int alloc(DevBuf &b, size_t bytes);
+  static BufferScope *current();
+
+ private:
+  static void give_back(void *self, void *p, size_t bytes);
+  std::vector<std::pair<void *, size_t>> kept_;
+  BufferScope *outer_ = nullptr;
+  int dev_ = 0;
+  bool idle_ = false;
+};
 
 // A simple owning device allocation; the engine keeps a few of these per call. An
 // allocator that takes blocks back (the engine's per-call Arena) sets give_back, and
@@ -130,6 +157,7 @@ struct DevBuf {
   int alloc(size_t b) {
     release();
     if (b == 0) return QFS_OK;
+    if (BufferScope *sc = BufferScope::current()) return sc->alloc(*this, b);
     hipError_t e = hipMalloc(&ptr, b);
     if (e == hipErrorOutOfMemory) {
       // blocks held for later calls go first

@@ -999,10 +999,8 @@ struct QdData {
     QFS_TRY(draw(np, M, Mnew, kRoleTrain, 0));
     QFS_TRY(targets(np, nf, Mnew));  // each column's output depends on that column alone
     QFS_HIP(hipStreamSynchronize(st));
-    std::swap(tpsi.ptr, np.ptr);
-    std::swap(tpsi.bytes, np.bytes);
-    std::swap(tphi.ptr, nf.ptr);
-    std::swap(tphi.bytes, nf.bytes);
+    tpsi.swap(np);
+    tphi.swap(nf);
     M = Mnew;
     ++generation;
     return draw_validation(M);
@@ -1354,6 +1352,7 @@ constexpr int kQdBatchStreams = 8;  // problems run side by side by the batched 
 int qd_entry(int d, const qfs_template *tmpl, const qfs_target *target, const qfs_params *params,
              const qfs_c128 *gates_in, qfs_c128 *gates_out, qfs_result *res, bool one_stream) {
   const double t0 = qd_now();
+  BufferScope scope;
   if (!target) {
     set_error_detail("qudits: null target");
     return QFS_EINVAL;
@@ -1377,7 +1376,8 @@ int qd_entry(int d, const qfs_template *tmpl, const qfs_target *target, const qf
     data.phi = target->phi;
     data.n_train = n_train;
     data.n_val = target->n_val;
-    return qd_instantiate_impl(d, tmpl, data, *params, gates_in, gates_out, res, t0);
+    QFS_TRY(qd_instantiate_impl(d, tmpl, data, *params, gates_in, gates_out, res, t0));
+    return scope.done(static_cast<hipStream_t>(params->hip_stream));
   }
   if (target->kind == QFS_TARGET_DENSE) {
     if (!target->U || N > (int64_t(1) << 16)) {
@@ -1404,7 +1404,8 @@ int qd_entry(int d, const qfs_template *tmpl, const qfs_target *target, const qf
   data.tgt = target;
   data.seed = params->seed;
   data.m_val = params->m_val;
-  return qd_instantiate_impl(d, tmpl, data, *params, gates_in, gates_out, res, t0);
+  QFS_TRY(qd_instantiate_impl(d, tmpl, data, *params, gates_in, gates_out, res, t0));
+  return scope.done(static_cast<hipStream_t>(params->hip_stream));
 }
 
 }  // namespace
@@ -1490,6 +1491,7 @@ int qfs_qudit_sweep(int32_t d, int32_t n, int32_t L, const int32_t *pairs, const
     return QFS_EINVAL;
   }
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  BufferScope scope;
   std::vector<int> all(starts);
   for (int s = 0; s < starts; ++s) all[s] = s;
   const int D = d * d;
@@ -1518,8 +1520,7 @@ int qfs_qudit_sweep(int32_t d, int32_t n, int32_t L, const int32_t *pairs, const
     QFS_TRY(w.forward(false));
     QFS_TRY(w.backward());
     QFS_HIP(hipMemcpyAsync(c_train, w.costs.ptr, sizeof(double) * starts, hipMemcpyDeviceToHost, st));
-    QFS_HIP(hipStreamSynchronize(st));
-    return QFS_OK;
+    return scope.done(st);
   };
   return precision == QFS_PREC_MIXED ? run(float{}) : run(double{});
 }

@@ -532,8 +532,8 @@ def qfs_polar_update(gamma, beta=0.0, u=None):
     """gamma [count, 4, 4]; returns the updated gates (a new tensor unless ``u`` given)."""
     import torch
     count = gamma.shape[0]
-    if u is None:
-        u = torch.zeros_like(gamma)
+    if u is None:  # (the library reads u only when beta != 0)
+        u = torch.empty_like(gamma) if beta == 0.0 else torch.zeros_like(gamma)
     _check(load().qfs_polar_update(count, _dev_c128(gamma, "gamma"), beta, _dev_c128(u, "u"),
                                    _stream()), "qfs_polar_update")
     return u
