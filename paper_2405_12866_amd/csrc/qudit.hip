@@ -15,6 +15,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <thread>
+#include <type_traits>
 #include <vector>
 
 #include "philox.h"
@@ -26,11 +27,28 @@ namespace {
 
 constexpr int kQdBlock = 256;
 constexpr int kQdMaxP = 64;  // environment partial blocks per (start, row group)
+// Environment blocks of a launch over every start (7 qutrits, 16 starts: 12.0 us a launch with
+// 400, 12.9 with 640, 14.6 with 1100, 18.0 with one item a thread).
+constexpr int kQdEnvBlocks = 400;
 constexpr int kQdMaxDD = 256;  // entries of the largest gate (d = 4: 16 x 16)
 // Jacobi stops when every column pair has |g_p^dagger g_q| <= tol |g_p| |g_q|. The Gram
 // entry of D-long columns carries a rounding error of about D eps |g_p| |g_q| (1e-15 for
 // D = 9), so the threshold sits above it; the polar factor is then accurate to ~1e-14.
 constexpr double kQdJacobiTol = 1e-14;
+
+// x / d by one high product for x < 2^31 (d > 1: mul = ceil(2^(31 + s) / d), s = ceil log2 d).
+struct QdDiv {
+  uint32_t d, mul, sh;
+};
+QdDiv qd_div(int64_t d) {
+  QdDiv v{(uint32_t)d, 0, 0};
+  if (d <= 1 || d >= (int64_t(1) << 31)) return v;
+  int s = 0;
+  while ((int64_t(1) << s) < d) ++s;
+  v.mul = (uint32_t)((((uint64_t)1 << (31 + s)) + (uint64_t)d - 1) / (uint64_t)d);
+  v.sh = (uint32_t)(s - 1);
+  return v;
+}
 
 // Position of a gate group: items are (group r, sample j), j fastest.
 struct QdGeom {
@@ -39,15 +57,28 @@ struct QdGeom {
   int64_t s_lo;     // d^(lower digit position of the two gate qudits)
   int64_t mid;      // d^(digits strictly between the two positions)
   int64_t sa, sb;   // strides of the gate's first and second qudit
+  QdDiv dM, dlo, dmid;
 };
 
+// Offset of item `it`'s first element (digits r_hi | 0 (upper gate qudit) | r_mid | 0 (lower
+// gate qudit) | r_lo, sample j). Sets below 2^31 elements in 32 bits with the divisions as
+// products: in 64 bits the five divisions of an item took longer than its gate product.
+__device__ __forceinline__ uint32_t qd_quot(uint32_t x, const QdDiv &v) {
+  return v.d == 1 ? x : __umulhi(x, v.mul) >> v.sh;
+}
 template <int d>
-__device__ __forceinline__ int64_t qd_base(const QdGeom &g, int64_t r) {
-  const int64_t r_lo = r % g.s_lo;
-  const int64_t t = r / g.s_lo;
-  const int64_t r_mid = t % g.mid, r_hi = t / g.mid;
-  // digits: r_hi | 0 (upper gate qudit) | r_mid | 0 (lower gate qudit) | r_lo
-  return r_hi * d * g.mid * d * g.s_lo + r_mid * d * g.s_lo + r_lo;
+__device__ __forceinline__ uint32_t qd_offset(const QdGeom &g, uint32_t it) {
+  const uint32_t r = qd_quot(it, g.dM), j = it - r * (uint32_t)g.M;
+  const uint32_t t = qd_quot(r, g.dlo), r_lo = r - t * (uint32_t)g.s_lo;
+  const uint32_t r_hi = qd_quot(t, g.dmid), r_mid = t - r_hi * (uint32_t)g.mid;
+  return (((r_hi * d * (uint32_t)g.mid + r_mid) * d) * (uint32_t)g.s_lo + r_lo) * (uint32_t)g.M + j;
+}
+template <int d>
+__device__ __forceinline__ int64_t qd_offset(const QdGeom &g, int64_t it) {
+  const int64_t r = it / g.M, j = it % g.M;
+  const int64_t t = r / g.s_lo, r_lo = r % g.s_lo;
+  const int64_t r_hi = t / g.mid, r_mid = t % g.mid;
+  return (((r_hi * d * g.mid + r_mid) * d) * g.s_lo + r_lo) * g.M + j;
 }
 
 QdGeom qd_geom(int d, int n, int M, int qa, int qb) {
@@ -65,16 +96,32 @@ QdGeom qd_geom(int d, int n, int M, int qa, int qb) {
   g.mid = pw(hi - lo - 1);
   g.sa = pw(pa);
   g.sb = pw(pb);
+  g.dM = qd_div(M);
+  g.dlo = qd_div(g.s_lo);
+  g.dmid = qd_div(g.mid);
   return g;
 }
 
-// dst = u_k src (dagger: u_k^dagger src) for every active start; the gate (FP64 master)
-// goes through LDS in the state precision.
-template <typename R, int d>
-__global__ __launch_bounds__(kQdBlock) void k_qd_apply(const cx<R> *src, int64_t src_stride, cx<R> *dst,
-                                                       int64_t dst_stride, const c128 *gates,
+// Whether a set's offsets fit the 32-bit forms.
+bool qd_narrow(const QdGeom &g, int d) { return g.groups * d * d * (int64_t)g.M < (int64_t(1) << 31); }
+
+// One set of an apply launch: dst = u_k src for every active start.
+template <typename R>
+struct QdSeg {
+  const cx<R> *src;
+  int64_t src_stride;
+  cx<R> *dst;
+  int64_t dst_stride;
+  QdGeom g;
+};
+
+// dst = u_k src (dagger: u_k^dagger src) for every active start and set (blockIdx.z: the
+// forward pass moves the training and the validation set with one launch); the gate (FP64
+// master) goes through LDS in the state precision.
+template <typename R, int d, typename Ix>
+__global__ __launch_bounds__(kQdBlock) void k_qd_apply(QdSeg<R> s0, QdSeg<R> s1, const c128 *gates,
                                                        int32_t gstride, int32_t k, int32_t dagger,
-                                                       QdGeom g, const int32_t *slots) {
+                                                       const int32_t *slots) {
   constexpr int D = d * d;
   __shared__ cx<R> u[D * D];
   const int s = slots[blockIdx.y];
@@ -85,22 +132,19 @@ __global__ __launch_bounds__(kQdBlock) void k_qd_apply(const cx<R> *src, int64_t
     u[e] = cmake<R>((R)v.re, (R)v.im);
   }
   __syncthreads();
-  const cx<R> *x = src + (int64_t)s * src_stride;
-  cx<R> *y = dst + (int64_t)s * dst_stride;
-  const int64_t items = g.groups * g.M;
-  for (int64_t it = blockIdx.x * (int64_t)kQdBlock + threadIdx.x; it < items;
-       it += (int64_t)gridDim.x * kQdBlock) {
-    const int64_t j = it % g.M, r = it / g.M;
-    const int64_t base = qd_base<d>(g, r);
-    int64_t off[D];
+  const QdSeg<R> &sg = blockIdx.z ? s1 : s0;
+  const QdGeom &g = sg.g;
+  const cx<R> *x = sg.src + (int64_t)s * sg.src_stride;
+  cx<R> *y = sg.dst + (int64_t)s * sg.dst_stride;
+  const Ix items = (Ix)(g.groups * g.M);
+  const Ix ra = (Ix)(g.sa * g.M), rb = (Ix)(g.sb * g.M);
+  for (Ix it = blockIdx.x * (Ix)kQdBlock + threadIdx.x; it < items; it += (Ix)gridDim.x * kQdBlock) {
+    const Ix base = qd_offset<d>(g, it);
     cx<R> in[D];
 #pragma unroll
     for (int a = 0; a < d; ++a)
 #pragma unroll
-      for (int b = 0; b < d; ++b) {
-        off[a * d + b] = (base + a * g.sa + b * g.sb) * g.M + j;
-        in[a * d + b] = x[off[a * d + b]];
-      }
+      for (int b = 0; b < d; ++b) in[a * d + b] = x[base + a * ra + b * rb];
     // (d > 2: output rows d at a time, so the compiler does not hold the whole gate in
     // registers across the item loop)
     constexpr int UQ = d == 2 ? D : d;
@@ -109,7 +153,7 @@ __global__ __launch_bounds__(kQdBlock) void k_qd_apply(const cx<R> *src, int64_t
       cx<R> acc = cmake<R>(0, 0);
 #pragma unroll
       for (int p = 0; p < D; ++p) cfma(acc, u[q * D + p], in[p]);
-      y[off[q]] = acc;
+      y[base + (Ix)(q / d) * ra + (Ix)(q % d) * rb] = acc;
     }
   }
 }
@@ -153,7 +197,7 @@ constexpr int qd_env_rows() {
 // Environment partials: block (row set xg, partial blk, start) accumulates rows
 // q = RY xg + y (y < RY) of Gamma[q][p] = sum a(q) conj(b(p)) over its items in FP64 and
 // writes them to partials[s][blk][q][p].
-template <typename R, int d>
+template <typename R, int d, typename Ix>
 __global__ __launch_bounds__(kQdBlock) void k_qd_env(const cx<R> *a, int64_t a_stride, const cx<R> *b,
                                                      int64_t b_stride, QdGeom g, int32_t P,
                                                      c128 *partials, const int32_t *slots) {
@@ -171,22 +215,22 @@ __global__ __launch_bounds__(kQdBlock) void k_qd_env(const cx<R> *a, int64_t a_s
   for (int y = 0; y < RY; ++y)
 #pragma unroll
     for (int p = 0; p < D; ++p) acc[y][p] = cmake(0.0, 0.0);
-  const int64_t items = g.groups * g.M;
-  for (int64_t it = blk * (int64_t)kQdBlock + threadIdx.x; it < items; it += (int64_t)P * kQdBlock) {
-    const int64_t j = it % g.M, r = it / g.M;
-    const int64_t base = qd_base<d>(g, r);
+  const Ix items = (Ix)(g.groups * g.M);
+  const Ix ra = (Ix)(g.sa * g.M), rb = (Ix)(g.sb * g.M);
+  for (Ix it = blk * (Ix)kQdBlock + threadIdx.x; it < items; it += (Ix)P * kQdBlock) {
+    const Ix base = qd_offset<d>(g, it);
     c128 bv[D], av[RY];
 #pragma unroll
     for (int x = 0; x < d; ++x)
 #pragma unroll
       for (int y = 0; y < d; ++y) {
-        const cx<R> v = bs[(base + x * g.sa + y * g.sb) * g.M + j];
+        const cx<R> v = bs[base + x * ra + y * rb];
         bv[x * d + y] = cmake((double)v.re, (double)v.im);
       }
 #pragma unroll
     for (int y = 0; y < RY; ++y) {
       const int q = xg * RY + y;  // local row: digits q / d (first qudit), q % d (second)
-      const cx<R> v = as[(base + (q / d) * g.sa + (q % d) * g.sb) * g.M + j];
+      const cx<R> v = as[base + (Ix)(q / d) * ra + (Ix)(q % d) * rb];
       av[y] = cmake((double)v.re, (double)v.im);
     }
 #pragma unroll
@@ -303,10 +347,167 @@ __device__ __noinline__ void qd_polar_singular(const c128 (*Gc)[16], const c128 
     }
 }
 
-constexpr int kQdFinBlock = 128;  // eight 16-lane rows: one column pair each (DM <= 16)
+constexpr int kQdFinBlock = 256;  // four waves; the Jacobi uses one 16-lane row per column pair
+
+// ------------------------------------------------------------------ polar factor by products
+// Unitary polar factor of a DM x DM matrix (4 < DM <= 16, zero-padded to 16 x 16) by odd
+// polynomials of degree five, X <- X (a I + b Y + c Y^2) with Y = X^dag X, which keep the polar
+// factor and move every singular value towards 1: three 16 x 16 complex products each, on the
+// FP64 matrix cores, one real product per wave (plane re / im of the result, half of the
+// inner index), so a stage is three phases of four 16x16x4 products a wave and a barrier.
+// Scaled by |A|_F the singular values lie in (0, 1]; the first four polynomials minimise
+// max |1 - p| over the interval the one before leaves, from [0.01, 1] on (found by linear
+// programming on a grid; they map it into 1 +- 0.0125), the others are the Taylor polynomial
+// of 1 / sqrt(Y) about I, whose error is (5 / 16) (I - Y)^3. An input near a multiple of a
+// unitary starts there. The factor is done when every entry of Y - I was below 1e-6 before a
+// step. Returns false when that does not happen (singular values below about 1e-3 |A|_F, or
+// none): the Jacobi SVD takes those.
+// Bound by the latency of its phases on one work-group, 6-7 stages of about 1600 cycles: the
+// whole finalize takes 12 us for 9 x 9 and 14 us for 16 x 16 environments, against 36 and 66
+// with the Jacobi SVD (some 7 sweeps of 9 or 15 rounds, a barrier each).
+typedef double qd_f64x4 __attribute__((ext_vector_type(4)));
+
+struct QdPolyLds {
+  // planes re / im, each as the two halves of the inner index (read as their sum)
+  double X[2][2][16][17], Y[2][2][16][17], Wm[2][2][16][17];
+  double red[4];
+};
+
+// Tm: the matrix (row-major DM x DM), Pu: its polar factor. Called by the whole block, after a
+// barrier; ends with one.
+template <int DM>
+__device__ bool qd_polar_poly(QdPolyLds &S, const c128 *Tm, c128 *Pu) {
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int plane = w & 1, half = w >> 1;
+  const int li = lane & 15, lk = lane >> 4;
+  const int er = t >> 4, ec = t & 15;
+  const bool in = er < DM && ec < DM;
+  const c128 x0 = in ? Tm[er * DM + ec] : cmake(0.0, 0.0);
+  double n2 = row16_sum(cabs2(x0));
+  n2 += __shfl_xor(n2, 16);
+  n2 += __shfl_xor(n2, 32);
+  if (lane == 0) S.red[w] = n2;
+  __syncthreads();
+  n2 = (S.red[0] + S.red[1]) + (S.red[2] + S.red[3]);
+  if (!(n2 > 1e-200 && n2 < 1e200)) return false;
+  const double inv = 1.0 / sqrt(n2);
+  S.X[0][0][er][ec] = x0.re * inv;
+  S.X[0][1][er][ec] = 0.0;
+  S.X[1][0][er][ec] = x0.im * inv;
+  S.X[1][1][er][ec] = 0.0;
+  __syncthreads();
+  auto get = [&](const double (&M)[2][2][16][17], int p, int r, int c) { return M[p][0][r][c] + M[p][1][r][c]; };
+  auto mma = [&](double a, double b, qd_f64x4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); };
+  auto put = [&](double (&M)[2][2][16][17], const qd_f64x4 &d) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) M[plane][half][lk + 4 * v][li] = d[v];
+  };
+  constexpr double kA[4] = {8.093369, 3.636586, 2.661300, 1.956172};
+  constexpr double kB[4] = {-23.620432, -2.721927, -1.977155, -1.337508};
+  constexpr double kC[4] = {17.446152, 0.536546, 0.452616, 0.383853};
+  bool near = false;
+  for (int st = 0; st < 12; ++st) {
+    // the last stages in the residual R = I - Y, X <- X + X R (I / 2 + (3 / 8) R): what is added
+    // is small, so X stays unitary to the rounding of its entries. The first stage is written in
+    // R = I - DM Y, small for a near multiple of a unitary (DM^(1/2) X is close to one).
+    const bool fin = st >= 4 || (near && st > 0);
+    const bool res = fin || st == 0;
+    const double ys = st == 0 ? (double)DM : 1.0;
+    double yr[2], yi[2];  // Y[8 half + 4 h + lk][li], or R
+    {
+      // Y = X^dag X: A[i][k] = conj(X[k][i]), B[k][j] = X[k][j]
+      qd_f64x4 acc = {0, 0, 0, 0};
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int k = 8 * half + 4 * h + lk;
+        const double xr = get(S.X, 0, k, li), xi = get(S.X, 1, k, li);
+        acc = mma(xr, plane ? xi : xr, acc);
+        acc = mma(plane ? -xi : xi, plane ? xr : xi, acc);
+      }
+      put(S.Y, acc);
+    }
+    __syncthreads();
+    // the wave's plane of X at its accumulator entries, for the first half's a X below (kept
+    // whole there: a X split over the halves would let them grow beyond their sum and lose digits)
+    double xs[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) xs[v] = half ? 0.0 : get(S.X, plane, lk + 4 * v, li);
+    double e2 = 0.0, f2 = 0.0;  // largest and sum of |R[..]|^2
+    {
+      // W = X Y (X R): A[i][k] = X[i][k], B[k][j] = Y[k][j]
+      qd_f64x4 acc = {0, 0, 0, 0};
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int k = 8 * half + 4 * h + lk;
+        yr[h] = get(S.Y, 0, k, li);
+        yi[h] = get(S.Y, 1, k, li);
+        const double dl = (k == li && k < DM) ? 1.0 : 0.0;
+        if (res) {
+          yr[h] = fma(-ys, yr[h], dl);
+          yi[h] = -ys * yi[h];
+        }
+        const double xr = get(S.X, 0, li, k), xi = get(S.X, 1, li, k);
+        acc = mma(xr, plane ? yi[h] : yr[h], acc);
+        acc = mma(plane ? xi : -xi, plane ? yr[h] : yi[h], acc);
+        const double r2 = fma(yr[h], yr[h], yi[h] * yi[h]);  // (used where yr, yi hold R)
+        e2 = fmax(e2, r2);
+        f2 += r2;
+      }
+      put(S.Wm, acc);
+    }
+    if (st == 0) {
+      f2 = row16_sum(f2);
+      f2 += __shfl_xor(f2, 16);
+      f2 += __shfl_xor(f2, 32);
+      if (lane == 0 && plane == 0) S.red[half] = f2;
+    }
+    const bool more = __syncthreads_or(!fin || !(e2 < 1e-12));
+    if (st == 0) near = S.red[0] + S.red[1] < 0.25;
+    double a = 1.0, b = 0.5, c = 0.375;
+    if (st == 0) {
+      if (near) {
+        const double r = sqrt((double)DM);
+        a *= r;
+        b *= r;
+        c *= r;
+      } else {  // kA + kB Y + kC Y^2 in powers of R, Y = (I - R) / DM
+        const double b1 = kB[0] / DM, c1 = kC[0] / (DM * DM);
+        a = kA[0] + b1 + c1;
+        b = -(b1 + 2.0 * c1);
+        c = c1;
+      }
+    } else if (!fin) {
+      a = kA[st];
+      b = kB[st];
+      c = kC[st];
+    }
+    {
+      // X <- a X + W (b I + c Y)
+      qd_f64x4 acc;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[v] = a * xs[v];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int k = 8 * half + 4 * h + lk;
+        const double wr = get(S.Wm, 0, li, k), wi = get(S.Wm, 1, li, k);
+        const double pr = fma(c, yr[h], k == li ? b : 0.0), pi = c * yi[h];
+        acc = mma(wr, plane ? pi : pr, acc);
+        acc = mma(plane ? wi : -wi, plane ? pr : pi, acc);
+      }
+      put(S.X, acc);
+    }
+    __syncthreads();
+    if (!more) {
+      if (in) Pu[er * DM + ec] = cmake(get(S.X, 0, er, ec), get(S.X, 1, er, ec));
+      __syncthreads();
+      return true;
+    }
+  }
+  return false;
+}
 
 // LDS workspace of one DM x DM polar update.
-template <int DM>
+template <int DM, bool PROD>
 struct QdPolarLds {
   static constexpr int PL = (DM + 1) / 2 * 2;  // players of the round-robin schedule
   c128 Gc[PL][16];   // G by columns: Gc[c][r] = G[r][c]
@@ -316,13 +517,30 @@ struct QdPolarLds {
   c128 Nm[DM * DM];  // V_prev^dagger V_prev
   c128 Pu[DM * DM];  // the polar factor (row-major) out
   double sig[DM];
+  std::conditional_t<PROD && (DM > 4), QdPolyLds, char> poly;
 };
 
-// The whole block: Pu <- the unitary polar factor of Tm, started from V_prev in Vs, and the
-// new right singular vectors into Vs (Tm and Vs filled and a barrier passed by the caller).
-template <int DM>
-__device__ void qd_polar_block(QdPolarLds<DM> &W) {
-  constexpr int PL = QdPolarLds<DM>::PL;
+// The whole block: Pu <- the unitary polar factor of Tm (Tm and Vs filled and a barrier passed
+// by the caller): the 4 x 4 routine, the matrix products above, or the Jacobi SVD started from
+// V_prev in Vs, which leaves the new right singular vectors there.
+//
+// PROD: the products first. They serve the complex64 sweeps. Complex128 sweeps keep the SVD:
+// a run in them ends at the rounding floor of its costs, where the generalisation test
+// compares rounding errors alone, and there the products' more exact factors (unitary to
+// 4e-16 against 5e-15) show the gates' fit to the rounding of the training outputs, a c_val /
+// c_train of 1 + 2 p / (M N) or so for p gate parameters, as over-training.
+template <int DM, bool PROD>
+__device__ void qd_polar_block(QdPolarLds<DM, PROD> &W) {
+  if constexpr (PROD && DM == 4) {
+    if (threadIdx.x < 64)
+      polar4_wave<float>(W.Tm, 0.0, nullptr, W.Pu, nullptr, &W.Gc[0][0], &W.Vc[0][0], W.sig, W.Vs);
+    __syncthreads();
+    return;
+  }
+  if constexpr (PROD && DM > 4) {
+    if (qd_polar_poly<DM>(W.poly, W.Tm, W.Pu)) return;
+  }
+  constexpr int PL = QdPolarLds<DM, PROD>::PL;
   constexpr int NP = PL / 2;  // pairs per round
   static_assert(DM <= 16 && NP * 16 <= kQdFinBlock, "one 16-lane row per pair");
   const int t = threadIdx.x;
@@ -461,12 +679,12 @@ __device__ __forceinline__ c128 qd_mix(c128 g, c128 u, double beta) {
   return beta != 0.0 ? cmake((1.0 - beta) * g.re + beta * u.re, (1.0 - beta) * g.im + beta * u.im) : g;
 }
 
-template <int d>
+template <int d, bool PROD>
 __global__ __launch_bounds__(kQdFinBlock) void k_qd_finalize(const c128 *partials, int32_t P, double beta,
                                                              const int32_t *slots, c128 *gates, c128 *vstore,
                                                              int32_t gstride, int32_t k) {
   constexpr int D = d * d;
-  __shared__ QdPolarLds<D> W;
+  __shared__ QdPolarLds<D, PROD> W;
   const int s = slots[blockIdx.x];
   c128 *u = gates + (int64_t)s * gstride + (int64_t)k * D * D;
   c128 *vst = vstore + (int64_t)s * gstride + (int64_t)k * D * D;
@@ -476,7 +694,7 @@ __global__ __launch_bounds__(kQdFinBlock) void k_qd_finalize(const c128 *partial
     W.Vs[e] = vst[e];
   }
   __syncthreads();
-  qd_polar_block<D>(W);
+  qd_polar_block<D, PROD>(W);
   for (int e = t; e < D * D; e += kQdFinBlock) {
     u[e] = W.Pu[e];
     vst[e] = W.Vs[e];
@@ -487,12 +705,12 @@ __global__ __launch_bounds__(kQdFinBlock) void k_qd_finalize(const c128 *partial
 // the trace of the slot's D x D environment over the spectator digit,
 // G1[x][y] = sum_z G[d x + z][d y + z]; v <- polar((1 - beta) G1 + beta v), written back as
 // v (x) I_d. Its warm-start V (d x d) sits at the slot positions (d x, d y) of the stored V.
-template <int d>
+template <int d, bool PROD>
 __global__ __launch_bounds__(kQdFinBlock) void k_qd_finalize1(const c128 *partials, int32_t P, double beta,
                                                               const int32_t *slots, c128 *gates, c128 *vstore,
                                                               int32_t gstride, int32_t k) {
   constexpr int D = d * d;
-  __shared__ QdPolarLds<d> W;
+  __shared__ QdPolarLds<d, PROD> W;
   __shared__ c128 Gf[D * D];
   const int s = slots[blockIdx.x];
   c128 *u = gates + (int64_t)s * gstride + (int64_t)k * D * D;
@@ -508,7 +726,7 @@ __global__ __launch_bounds__(kQdFinBlock) void k_qd_finalize1(const c128 *partia
     W.Vs[e] = vst[(d * x) * D + d * y];
   }
   __syncthreads();
-  qd_polar_block<d>(W);
+  qd_polar_block<d, PROD>(W);
   for (int e = t; e < D * D; e += kQdFinBlock) {
     const int r = e / D, c = e % D;
     u[e] = (r % d == c % d) ? W.Pu[(r / d) * d + c / d] : cmake(0.0, 0.0);
@@ -675,20 +893,31 @@ struct QdSweeper {
   // P depends on the geometry only, and the partials are indexed by start, so
   // launches over disjoint start sets never share them)
   template <int dd>
-  int apply_t(const cx<R> *src, int64_t ss, cx<R> *dst, int64_t ds, int k, bool dagger, int Mrows,
-              const int32_t *sl, int ns, hipStream_t s) {
-    const int qa = pairs[2 * k], qb = pairs[2 * k + 1];
-    const QdGeom g = qd_geom(dd, n, Mrows, qa, qb);
-    hipLaunchKernelGGL((k_qd_apply<R, dd>), dim3(qd_grid(g.groups * Mrows), ns), dim3(kQdBlock), 0, s, src, ss,
-                       dst, ds, g64, L * dd * dd * dd * dd, k, dagger ? 1 : 0, g, sl);
+  int apply_t(const QdSeg<R> &s0, const QdSeg<R> *s1, int k, bool dagger, const int32_t *sl, int ns, hipStream_t s) {
+    const int64_t i0 = s0.g.groups * s0.g.M, i1 = s1 ? s1->g.groups * s1->g.M : 0;
+    const dim3 grid(qd_grid(std::max(i0, i1)), ns, s1 ? 2 : 1);
+    const int gs = L * dd * dd * dd * dd;
+    if (qd_narrow(s0.g, dd) && (!s1 || qd_narrow(s1->g, dd)))
+      hipLaunchKernelGGL((k_qd_apply<R, dd, uint32_t>), grid, dim3(kQdBlock), 0, s, s0, s1 ? *s1 : s0, g64, gs, k,
+                         dagger ? 1 : 0, sl);
+    else
+      hipLaunchKernelGGL((k_qd_apply<R, dd, int64_t>), grid, dim3(kQdBlock), 0, s, s0, s1 ? *s1 : s0, g64, gs, k,
+                         dagger ? 1 : 0, sl);
     QFS_HIP(hipGetLastError());
     return QFS_OK;
   }
+  QdSeg<R> seg(const cx<R> *src, int64_t ss, cx<R> *dst, int64_t ds, int k, int Mrows) const {
+    return QdSeg<R>{src, ss, dst, ds, qd_geom(d, n, Mrows, pairs[2 * k], pairs[2 * k + 1])};
+  }
+  int apply_segs(const QdSeg<R> &s0, const QdSeg<R> *s1, int k, bool dagger, const int32_t *sl, int ns,
+                 hipStream_t s) {
+    return d == 2   ? apply_t<2>(s0, s1, k, dagger, sl, ns, s)
+           : d == 3 ? apply_t<3>(s0, s1, k, dagger, sl, ns, s)
+                    : apply_t<4>(s0, s1, k, dagger, sl, ns, s);
+  }
   int apply_on(const cx<R> *src, int64_t ss, cx<R> *dst, int64_t ds, int k, bool dagger, int Mrows,
                const int32_t *sl, int ns, hipStream_t s) {
-    return d == 2   ? apply_t<2>(src, ss, dst, ds, k, dagger, Mrows, sl, ns, s)
-           : d == 3 ? apply_t<3>(src, ss, dst, ds, k, dagger, Mrows, sl, ns, s)
-                    : apply_t<4>(src, ss, dst, ds, k, dagger, Mrows, sl, ns, s);
+    return apply_segs(seg(src, ss, dst, ds, k, Mrows), nullptr, k, dagger, sl, ns, s);
   }
   int apply(const cx<R> *src, int64_t ss, cx<R> *dst, int64_t ds, int k, bool dagger, int Mrows) {
     return apply_on(src, ss, dst, ds, k, dagger, Mrows, slots.as<int32_t>(), nslots, st);
@@ -697,15 +926,25 @@ struct QdSweeper {
   int env_t(const cx<R> *a, int64_t as, const cx<R> *b, int64_t bs, int k, const int32_t *sl, int ns,
             hipStream_t s) {
     const QdGeom g = qd_geom(dd, n, M, pairs[2 * k], pairs[2 * k + 1]);
-    const int P = (int)std::max<int64_t>(1, std::min<int64_t>(kQdMaxP, (g.groups * M + kQdBlock - 1) / kQdBlock));
-    hipLaunchKernelGGL((k_qd_env<R, dd>), dim3(dd * dd / qd_env_rows<dd>() * P, ns), dim3(kQdBlock), 0, s, a, as,
-                       b, bs, g, P, partials.as<c128>(), sl);
+    // blocks per start and row set: the wave sums of a block's 2 RY D values cost as much as
+    // some five items of a thread, so a launch over every start has about kQdEnvBlocks blocks,
+    // enough to fill the device, and no more (the count follows the call's starts, not those
+    // still running, so a start's sums do not depend on the others)
+    constexpr int NX = dd * dd / qd_env_rows<dd>();
+    const int64_t most = std::min<int64_t>(kQdMaxP, (g.groups * M + kQdBlock - 1) / kQdBlock);
+    const int P = (int)std::max<int64_t>(1, std::min<int64_t>(most, (kQdEnvBlocks + NX * S - 1) / (NX * S)));
+    if (qd_narrow(g, dd))
+      hipLaunchKernelGGL((k_qd_env<R, dd, uint32_t>), dim3(NX * P, ns), dim3(kQdBlock), 0, s, a, as, b, bs, g, P,
+                         partials.as<c128>(), sl);
+    else
+      hipLaunchKernelGGL((k_qd_env<R, dd, int64_t>), dim3(NX * P, ns), dim3(kQdBlock), 0, s, a, as, b, bs, g, P,
+                         partials.as<c128>(), sl);
     QFS_HIP(hipGetLastError());
     if (kinds && kinds[k] == QFS_GATE_1Q)
-      hipLaunchKernelGGL((k_qd_finalize1<dd>), dim3(ns), dim3(kQdFinBlock), 0, s, partials.as<c128>(), P, beta, sl,
+      hipLaunchKernelGGL((k_qd_finalize1<dd, sizeof(R) == 4>), dim3(ns), dim3(kQdFinBlock), 0, s, partials.as<c128>(), P, beta, sl,
                          g64, vst, L * dd * dd * dd * dd, k);
     else
-      hipLaunchKernelGGL((k_qd_finalize<dd>), dim3(ns), dim3(kQdFinBlock), 0, s, partials.as<c128>(), P, beta, sl,
+      hipLaunchKernelGGL((k_qd_finalize<dd, sizeof(R) == 4>), dim3(ns), dim3(kQdFinBlock), 0, s, partials.as<c128>(), P, beta, sl,
                          g64, vst, L * dd * dd * dd * dd, k);
     QFS_HIP(hipGetLastError());
     return QFS_OK;
@@ -759,22 +998,22 @@ struct QdSweeper {
   // forward: B list from the current gates; with_c0: cost of the current gates
   // (costs[2S + s]); validation cost (costs[S + s]) when Mv > 0
   int forward(bool with_c0) {
-    cx<R> *P0 = psi.as<cx<R>>(), *B = blist.as<cx<R>>();
-    const int64_t sN = set(), bstride = sN * std::max(L - 1, 1);
-    for (int k = 0; k < L - 1; ++k)
-      QFS_TRY(apply(k == 0 ? P0 : B + (k - 1) * sN, k == 0 ? 0 : bstride, B + k * sN, bstride, k, false, M));
+    cx<R> *P0 = psi.as<cx<R>>(), *B = blist.as<cx<R>>(), *V = vstate.as<cx<R>>();
+    const int64_t sN = set(), bstride = sN * std::max(L - 1, 1), vN = N * Mv;
+    for (int k = 0; k < L; ++k) {
+      const QdSeg<R> vs = Mv > 0 ? seg(k == 0 ? psiv.as<cx<R>>() : V, k == 0 ? 0 : vN, V, vN, k, Mv) : QdSeg<R>{};
+      if (k < L - 1)
+        QFS_TRY(apply_segs(seg(k == 0 ? P0 : B + (k - 1) * sN, k == 0 ? 0 : bstride, B + k * sN, bstride, k, M),
+                           Mv > 0 ? &vs : nullptr, k, false, slots.as<int32_t>(), nslots, st));
+      else if (Mv > 0)
+        QFS_TRY(apply_segs(vs, nullptr, k, false, slots.as<int32_t>(), nslots, st));
+    }
     if (with_c0) {
       cx<R> *A = astate.as<cx<R>>();
       QFS_TRY(apply(L == 1 ? P0 : B + (L - 2) * sN, L == 1 ? 0 : bstride, A, sN, L - 1, false, M));
       QFS_TRY(dist(A, sN, phi.as<cx<R>>(), 0, sN, M, costs.as<double>() + 2 * S));
     }
-    if (Mv > 0) {
-      cx<R> *V = vstate.as<cx<R>>();
-      const int64_t vN = N * Mv;
-      for (int k = 0; k < L; ++k)
-        QFS_TRY(apply(k == 0 ? psiv.as<cx<R>>() : V, k == 0 ? 0 : vN, V, vN, k, false, Mv));
-      QFS_TRY(dist(V, vN, phiv.as<cx<R>>(), 0, vN, Mv, costs.as<double>() + S));
-    }
+    if (Mv > 0) QFS_TRY(dist(V, vN, phiv.as<cx<R>>(), 0, vN, Mv, costs.as<double>() + S));
     return QFS_OK;
   }
 
@@ -914,9 +1153,12 @@ template <int dd>
 int qd_apply_circuit(int n, int cols, c128 *x, const qfs_template *ct, const c128 *gates, const int32_t *slot0,
                      hipStream_t st) {
   for (int k = 0; k < ct->n_gates; ++k) {
-    const QdGeom g = qd_geom(dd, n, cols, ct->pairs[2 * k], ct->pairs[2 * k + 1]);
-    hipLaunchKernelGGL((k_qd_apply<double, dd>), dim3(qd_grid(g.groups * cols), 1), dim3(kQdBlock), 0, st, x,
-                       (int64_t)0, x, (int64_t)0, gates, 0, k, 0, g, slot0);
+    const QdSeg<double> g{x, 0, x, 0, qd_geom(dd, n, cols, ct->pairs[2 * k], ct->pairs[2 * k + 1])};
+    const dim3 grid(qd_grid(g.g.groups * cols), 1);
+    if (qd_narrow(g.g, dd))
+      hipLaunchKernelGGL((k_qd_apply<double, dd, uint32_t>), grid, dim3(kQdBlock), 0, st, g, g, gates, 0, k, 0, slot0);
+    else
+      hipLaunchKernelGGL((k_qd_apply<double, dd, int64_t>), grid, dim3(kQdBlock), 0, st, g, g, gates, 0, k, 0, slot0);
     QFS_HIP(hipGetLastError());
   }
   return QFS_OK;
