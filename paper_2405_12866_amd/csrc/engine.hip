@@ -965,8 +965,11 @@ int Group::make_targets(DevBuf &psi, DevBuf &phi, int M, int ld, hipStream_t s) 
                          cmake(0.0, 0.0), phi.as<c128>(), ld, s));
     return QFS_OK;
   }
-  QFS_HIP(hipMemcpyAsync(phi.ptr, psi.ptr, sizeof(c128) * (size_t)N_ * ld, hipMemcpyDeviceToDevice, s));
   const qfs_template *ct = tgt_->circuit;
+  if (circuit_fits(n_))  // every column of the master: the padding ones stay zero
+    return launch_circuit(n_, ld, psi.as<c128>(), phi.as<c128>(), ld, 1, ct->n_gates, ct->pairs,
+                          reinterpret_cast<const c128 *>(tgt_->circuit_gates), false, s);
+  QFS_HIP(hipMemcpyAsync(phi.ptr, psi.ptr, sizeof(c128) * (size_t)N_ * ld, hipMemcpyDeviceToDevice, s));
   const Geometry g{n_, (int32_t)N_, ceil_log2(ld), 1, M};  // the master is one chunk
   GateRef gr{reinterpret_cast<const c128 *>(tgt_->circuit_gates),
              reinterpret_cast<const c128 *>(tgt_->circuit_gates), 0};
@@ -1949,6 +1952,13 @@ int qfs_apply_gates(int32_t n, int32_t M, qfs_c128 *states, int32_t L, const int
   QFS_TRY(validate_template(&t));
   if (M < 1 || !states || !gates) return QFS_EINVAL;
   hipStream_t s = as_stream(hip_stream);
+  if (circuit_fits(n)) {
+    c128 *x = reinterpret_cast<c128 *>(states);
+    QFS_TRY(launch_circuit(n, M, x, x, 1, int64_t(1) << n, L, pairs, reinterpret_cast<const c128 *>(gates),
+                           dagger != 0, s));
+    QFS_HIP(hipStreamSynchronize(s));
+    return QFS_OK;
+  }
   BufferScope scope;
   const Geometry g = api_geometry(n, M);
   DevBuf A, slot;

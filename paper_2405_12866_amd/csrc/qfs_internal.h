@@ -199,6 +199,13 @@ struct DevBuf {
 };
 
 // ------------------------------------------------------------------ kernels (host API)
+// The gates of a list applied in order (dagger: u^dagger, last gate first) to M FP64 states in
+// one launch (circuit.hip): element (amplitude i, sample j) of src and dst (which may be the
+// same) at i si + j sj, one of si and sj being 1. For 2 to 13 qubits (circuit_fits).
+bool circuit_fits(int n);
+int launch_circuit(int n, int M, const c128 *src, c128 *dst, int64_t si, int64_t sj, int L, const int32_t *pairs,
+                   const c128 *gates, bool dagger, hipStream_t s);
+
 // Random numbers (rng.hip). Philox roles of the drawn sets: training states, validation
 // states (stream = the validation set's generation), initial gates (stream = start).
 enum { kRoleTrain = 1, kRoleVal = 2, kRoleInit = 3 };
