@@ -1980,15 +1980,18 @@ int qfs_dense_apply(int32_t n, int32_t M, const qfs_c128 *U, const qfs_c128 *psi
                     void *hip_stream) {
   if (n < 1 || n > 16 || M < 1 || !U || !psi || !out) return QFS_EINVAL;
   hipStream_t s = as_stream(hip_stream);
+  const int64_t N = int64_t(1) << n;
   BufferScope scope;
-  const int64_t N = int64_t(1) << n, ld = master_ld(M);
-  DevBuf A, B;
-  QFS_TRY(A.alloc(sizeof(c128) * N * ld));
-  QFS_TRY(B.alloc(sizeof(c128) * N * ld));
-  QFS_TRY(launch_to_internal<double>(n, M, ceil_log2(ld), 1, reinterpret_cast<const c128 *>(psi), A.as<c128>(), s));
-  QFS_TRY(launch_zgemm(false, (int)N, (int)ld, (int)N, cmake(1.0, 0.0), reinterpret_cast<const c128 *>(U),
-                       (int)N, A.as<c128>(), (int)ld, cmake(0.0, 0.0), B.as<c128>(), (int)ld, s));
-  QFS_TRY(launch_from_internal<double>(n, M, ceil_log2(ld), B.as<c128>(), reinterpret_cast<c128 *>(out), s));
+  // an output that overlaps an input is formed apart
+  auto overlaps = [&](const qfs_c128 *p, int64_t count) { return out < p + count && p < out + (int64_t)M * N; };
+  DevBuf tmp;
+  c128 *dst = reinterpret_cast<c128 *>(out);
+  if (overlaps(psi, (int64_t)M * N) || overlaps(U, N * N)) {
+    QFS_TRY(tmp.alloc(sizeof(c128) * M * N));
+    dst = tmp.as<c128>();
+  }
+  QFS_TRY(launch_dense_rows(N, M, reinterpret_cast<const c128 *>(U), reinterpret_cast<const c128 *>(psi), dst, s));
+  if (tmp.ptr) QFS_HIP(hipMemcpyAsync(out, dst, sizeof(c128) * M * N, hipMemcpyDeviceToDevice, s));
   return scope.done(s);
 }
 

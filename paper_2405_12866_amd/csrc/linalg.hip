@@ -7,75 +7,170 @@
 namespace qfs {
 
 // ------------------------------------------------------------------ ZGEMM
-// 32x32 output tile per 256-thread block, K tiles of 16 staged in LDS; each thread
-// owns a 2x2 sub-tile at rows ty, ty+16 and columns tx, tx+16.
-template <bool CT>
-__global__ __launch_bounds__(256) void k_zgemm(int m, int n, int k, c128 alpha, const c128 *A,
-                                               int lda, const c128 *B, int ldb, c128 beta,
-                                               c128 *C, int ldc) {
-  __shared__ c128 As[16][33];
-  __shared__ c128 Bs[16][33];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int i0 = blockIdx.y * 32, j0 = blockIdx.x * 32;
-  c128 acc[2][2];
-  for (int a = 0; a < 2; ++a)
-    for (int b = 0; b < 2; ++b) acc[a][b] = cmake(0.0, 0.0);
-  for (int kb = 0; kb < k; kb += 16) {
-    for (int e = tid; e < 512; e += 256) {
-      int ii, kk;
-      if (CT) {
-        ii = e & 31;
-        kk = e >> 5;
-      } else {
-        kk = e & 15;
-        ii = e >> 4;
-      }
-      const int gi = i0 + ii, gk = kb + kk;
-      c128 v = cmake(0.0, 0.0);
-      if (gi < m && gk < k) v = CT ? cconj(A[(int64_t)gk * lda + gi]) : A[(int64_t)gi * lda + gk];
-      As[kk][ii] = v;
-    }
-    for (int e = tid; e < 512; e += 256) {
-      const int jj = e & 31, kk = e >> 5;
-      const int gj = j0 + jj, gk = kb + kk;
-      Bs[kk][jj] = (gk < k && gj < n) ? B[(int64_t)gk * ldb + gj] : cmake(0.0, 0.0);
-    }
-    __syncthreads();
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// A matrix operand: element (r, c) at p[r rs + c cs].
+template <typename T>
+struct ZMat {
+  T *p;
+  int64_t rs, cs;
+};
+
+// C = alpha op(A) B + beta C, op(A) = A or conj(A) (a conjugate transpose by its strides).
+// A work-group has one 32 x 32 tile of C; its four waves take every fourth block of eight k
+// each and add their tiles in wave order at the end, so a product with few tiles still keeps
+// every SIMD busy. A wave forms its tile as 2 x 2 blocks of 16x16x4 FP64 matrix-core products
+// (four real ones per complex one), the operands loaded straight from memory in the layout the
+// instruction wants (lane l: row l % 16, k l / 16), three blocks ahead: each element is read by
+// one lane, and a k-step's sixteen products last 1024 cycles, so LDS staging would save nothing.
+// Bound by the FP64 matrix rate: 2048 x 100 x 2048 (11 qubits, 100 states) takes 95 us, 45 TFLOP/s
+// over the tiles' 128 columns; a 32 x 32 tile per 256 threads through LDS, with a load round trip
+// exposed in each of its 128 k tiles, took 310.
+template <bool CONJ>
+__global__ __launch_bounds__(256) void k_zgemm(int m, int n, int k, c128 alpha, ZMat<const c128> A,
+                                               ZMat<const c128> B, c128 beta, ZMat<c128> C) {
+  __shared__ c128 red[3][32][33];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int li = lane & 15, lk = lane >> 4;
+  // tiles of one row of C on one XCD (consecutive work-groups go round the eight), near in time,
+  // so that its rows of A come from memory once and from that XCD's L2 after
+  const int nx = (n + 31) / 32, seq = blockIdx.x >> 3;
+  const int i0 = ((seq / nx) * 8 + (blockIdx.x & 7)) * 32, j0 = (seq % nx) * 32;
+  if (i0 >= m) return;
+  // (rows and columns beyond the matrix read its last one; their results are not stored)
+  const c128 *ap[2], *bp[2];
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      const c128 a0 = As[kk][ty], a1 = As[kk][ty + 16];
-      const c128 b0 = Bs[kk][tx], b1 = Bs[kk][tx + 16];
-      cfma(acc[0][0], a0, b0);
-      cfma(acc[0][1], a0, b1);
-      cfma(acc[1][0], a1, b0);
-      cfma(acc[1][1], a1, b1);
-    }
-    __syncthreads();
+  for (int h = 0; h < 2; ++h) {
+    ap[h] = A.p + (int64_t)min(i0 + 16 * h + li, m - 1) * A.rs;
+    bp[h] = B.p + (int64_t)min(j0 + 16 * h + li, n - 1) * B.cs;
   }
-  const bool read_c = !(beta.re == 0.0 && beta.im == 0.0);
-  for (int a = 0; a < 2; ++a)
-    for (int b = 0; b < 2; ++b) {
-      const int gi = i0 + ty + 16 * a, gj = j0 + tx + 16 * b;
-      if (gi < m && gj < n) {
-        c128 v = alpha * acc[a][b];
-        if (read_c) v = v + beta * C[(int64_t)gi * ldc + gj];
-        C[(int64_t)gi * ldc + gj] = v;
+  f64x4 re[2][2], im[2][2];
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y) re[x][y] = im[x][y] = f64x4{0, 0, 0, 0};
+  // block of eight k: two steps of four, [step][half]
+  struct Blk {
+    c128 a[2][2], b[2][2];
+  };
+  auto load = [&](int kb, Blk &d) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int64_t kk = kb + 4 * t + lk;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        d.a[t][h] = ap[h][kk * A.cs];
+        d.b[t][h] = bp[h][kk * B.rs];
       }
     }
+  };
+  auto mma = [&](const Blk &d) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        const double ar = d.a[t][x].re, ai = CONJ ? -d.a[t][x].im : d.a[t][x].im;
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+          const double br = d.b[t][y].re, bi = d.b[t][y].im;
+          re[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, br, re[x][y], 0, 0, 0);
+          im[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, bi, im[x][y], 0, 0, 0);
+          re[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(-ai, bi, re[x][y], 0, 0, 0);
+          im[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, br, im[x][y], 0, 0, 0);
+        }
+      }
+  };
+  // whole blocks, three in flight (a load past the wave's last block repeats it)
+  constexpr int kStep = 32;  // eight per wave
+  const int kfull = k & ~7;
+  int kb = 8 * w;
+  if (kb < kfull) {
+    const int last = kfull - 8 - ((kfull - 8 - kb) & 31);
+    Blk d0, d1, d2;
+    load(kb, d0);
+    load(min(kb + kStep, last), d1);
+    load(min(kb + 2 * kStep, last), d2);
+    for (;;) {
+      mma(d0);
+      load(min(kb + 3 * kStep, last), d0);
+      kb += kStep;
+      if (kb > last) break;
+      mma(d1);
+      load(min(kb + 3 * kStep, last), d1);
+      kb += kStep;
+      if (kb > last) break;
+      mma(d2);
+      load(min(kb + 3 * kStep, last), d2);
+      kb += kStep;
+      if (kb > last) break;
+    }
+  }
+  if (w == 0 && kfull < k) {
+    Blk d;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int kk = kfull + 4 * t + lk;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        d.a[t][h] = kk < k ? ap[h][kk * A.cs] : cmake(0.0, 0.0);
+        d.b[t][h] = kk < k ? bp[h][kk * B.rs] : cmake(0.0, 0.0);
+      }
+    }
+    mma(d);
+  }
+  if (w > 0) {
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int y = 0; y < 2; ++y)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[w - 1][16 * x + lk + 4 * v][16 * y + li] = cmake(re[x][y][v], im[x][y][v]);
+  }
+  __syncthreads();
+  if (w > 0) return;
+  const bool read_c = !(beta.re == 0.0 && beta.im == 0.0);
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int r = 16 * x + lk + 4 * v, c = 16 * y + li;
+        const int gi = i0 + r, gj = j0 + c;
+        if (gi >= m || gj >= n) continue;
+        c128 s = cmake(re[x][y][v], im[x][y][v]);
+#pragma unroll
+        for (int o = 0; o < 3; ++o) s = s + red[o][r][c];
+        s = alpha * s;
+        c128 *dst = C.p + gi * C.rs + gj * C.cs;
+        if (read_c) s = s + beta * *dst;
+        *dst = s;
+      }
+}
+
+static int zgemm_go(bool conj_a, int m, int n, int k, c128 alpha, ZMat<const c128> A, ZMat<const c128> B, c128 beta,
+                    ZMat<c128> C, hipStream_t s) {
+  if (m <= 0 || n <= 0) return QFS_OK;
+  const int64_t tiles = ((m + 31) / 32 + 7) / 8 * 8 * (int64_t)((n + 31) / 32);
+  const dim3 grid((unsigned)tiles);
+  if (conj_a)
+    hipLaunchKernelGGL(k_zgemm<true>, grid, dim3(256), 0, s, m, n, k, alpha, A, B, beta, C);
+  else
+    hipLaunchKernelGGL(k_zgemm<false>, grid, dim3(256), 0, s, m, n, k, alpha, A, B, beta, C);
+  QFS_HIP(hipGetLastError());
+  return QFS_OK;
 }
 
 int launch_zgemm(bool conjtrans_a, int m, int n, int k, c128 alpha, const c128 *A, int lda,
                  const c128 *B, int ldb, c128 beta, c128 *C, int ldc, hipStream_t s) {
-  if (m <= 0 || n <= 0) return QFS_OK;
-  dim3 grid((n + 31) / 32, (m + 31) / 32);
-  if (conjtrans_a)
-    hipLaunchKernelGGL(k_zgemm<true>, grid, dim3(256), 0, s, m, n, k, alpha, A, lda, B, ldb,
-                       beta, C, ldc);
-  else
-    hipLaunchKernelGGL(k_zgemm<false>, grid, dim3(256), 0, s, m, n, k, alpha, A, lda, B, ldb,
-                       beta, C, ldc);
-  QFS_HIP(hipGetLastError());
-  return QFS_OK;
+  return zgemm_go(conjtrans_a, m, n, k, alpha,
+                  conjtrans_a ? ZMat<const c128>{A, 1, lda} : ZMat<const c128>{A, lda, 1},
+                  ZMat<const c128>{B, ldb, 1}, beta, ZMat<c128>{C, ldc, 1}, s);
+}
+
+int launch_dense_rows(int64_t N, int M, const c128 *U, const c128 *psi, c128 *out, hipStream_t s) {
+  return zgemm_go(false, (int)N, M, (int)N, cmake(1.0, 0.0), ZMat<const c128>{U, N, 1}, ZMat<const c128>{psi, 1, N},
+                  cmake(0.0, 0.0), ZMat<c128>{out, 1, N}, s);
 }
 
 // C = A^H B for a short, wide product (m x n output, k >> m, n; the Gram matrices of

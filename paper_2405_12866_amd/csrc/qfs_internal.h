@@ -227,6 +227,8 @@ int launch_kind_gates(uint64_t seed, int32_t start0, int32_t starts, int32_t L,
 // C[m x n] = alpha * op(A) * B + beta * C, op(A) = A (m x k) or A^H (A is k x m).
 int launch_zgemm(bool conjtrans_a, int m, int n, int k, c128 alpha, const c128 *A, int lda,
                  const c128 *B, int ldb, c128 beta, c128 *C, int ldc, hipStream_t s);
+// out = U psi for sample-major sets: U [N][N] row-major, psi and out [M][N].
+int launch_dense_rows(int64_t N, int M, const c128 *U, const c128 *psi, c128 *out, hipStream_t s);
 // Orthonormalise columns [c0, c1) of the rows x ld matrix A against columns [0, c0)
 // and among themselves: QR with real positive diag(R) (CholeskyQR2 after two block
 // Gram-Schmidt projections). Uses `work` (device, >= work_bytes_orth(rows, c1)). With
