@@ -80,6 +80,14 @@ struct BatchArgs {
   size_t scratch_slot_bytes;
 };
 
+// Bytes of a job's two working sets in the packet layout of k_batch_sweep, without and (of the
+// class that holds them) with their padding.
+inline size_t batch_set_bytes(int M, int Mv, int n, bool fp64) {
+  const int V = fp64 ? 1 : 2, top = M > Mv ? M : Mv;
+  return ((size_t)((top + V - 1) / V) + (size_t)((M + V - 1) / V)) * ((size_t)16 << n);
+}
+inline size_t batch_padded_bytes(size_t bytes) { return bytes + bytes / 16 + 1024; }
+
 // Per-problem options of the batched engine (all nullable / zero = the plain method).
 struct BatchOpts {
   const int32_t *m_init = nullptr;  // [P] initial sample count per problem

@@ -16,6 +16,7 @@
 #include "philox.h"
 #include "polar2.h"
 #include "polar4.h"
+#include "stream_common.h"
 
 namespace qfs {
 
@@ -28,10 +29,12 @@ __device__ __forceinline__ R bwave_sum(R x) {
   return x;
 }
 
+// Zero bits put in at positions lo < hi: each moves the bits from its position on up by one,
+// which adds that part once more. Bits beyond a state's index (the sample number of a flat
+// [rows][N] group index) move along, so the result indexes the whole set.
 __device__ __forceinline__ uint32_t deposit2(uint32_t r, int lo, int hi) {
-  r = ((r >> lo) << (lo + 1)) | (r & ((1u << lo) - 1u));
-  r = ((r >> hi) << (hi + 1)) | (r & ((1u << hi) - 1u));
-  return r;
+  r += r & ~((1u << lo) - 1u);
+  return r + (r & ~((1u << hi) - 1u));
 }
 
 // Wave sums of the 16 complex entries of a 4x4 environment (32 reals, FP64) by recursive
@@ -81,74 +84,160 @@ __device__ __forceinline__ double block_sum(double x, double *red) {
   return t;
 }
 
-// Apply u (or u^dagger) of qubit bit positions (pa, pb) to `rows` states of N amplitudes
-// stored contiguously ([rows][N]) in `st`.
-template <typename R, int NT>
-__device__ __forceinline__ void apply_states(cx<R> *st, int rows, int n, int pa, int pb,
-                                             const cx<R> *u, bool dagger) {
-  cx<R> m[16];
+// Pointers of known address space: through generic ones (a problem's pointers come out of
+// memory, and the sets lie in LDS or in global scratch) every access is a flat one.
+template <typename T>
+using gptr = __attribute__((address_space(1))) T *;
+template <typename T>
+__device__ __forceinline__ gptr<T> as_global(T *p) {
+  return (gptr<T>)p;
+}
+
+// A working set: packets of V samples of one amplitude (16 bytes: two complex64 or one
+// complex128), packet (j / V) 2^n + i for samples j .. and amplitude i, at slot pk + pk / 16
+// (16 bytes of padding per 256, so the groups of gates on the lowest bits fall on different
+// banks). Samples beyond the set's rows are zero.
+__device__ __forceinline__ uint32_t bslot(uint32_t pk) { return pk + (pk >> 4); }
+
+template <typename R>
+struct BSet {
+  Pk<R> *p;          // (LDS or scratch)
+  uint32_t packets;  // packet rows << n
+  __device__ __forceinline__ BSet(Pk<R> *p_, int rows, int n)
+      : p(p_), packets((uint32_t)((rows + Pk<R>::V - 1) / Pk<R>::V) << n) {}
+  __device__ __forceinline__ BSet(Pk<R> *p_, uint32_t packets_) : p(p_), packets(packets_) {}
+};
+
+template <typename R>
+__device__ __forceinline__ void gate_regs(const cx<R> *u, bool dagger, cx<R> (&m)[16]) {
 #pragma unroll
   for (int q = 0; q < 4; ++q)
 #pragma unroll
     for (int p = 0; p < 4; ++p) m[q * 4 + p] = dagger ? cconj(u[p * 4 + q]) : u[q * 4 + p];
+}
+
+// Apply u (or u^dagger) of qubit bit positions (pa, pb) to a set.
+template <typename R, int NT>
+__device__ __forceinline__ void apply_states(BSet<R> S, int pa, int pb, const cx<R> *u, bool dagger) {
+  constexpr int V = Pk<R>::V;
+  cx<R> m[16];
+  gate_regs<R>(u, dagger, m);
   const int lo = min(pa, pb), hi = max(pa, pb);
   const uint32_t ma = 1u << pa, mb = 1u << pb;
-  const uint32_t gper = 1u << (n - 2);
-  const uint32_t total = gper * rows;
-  // two groups per iteration: both groups' loads are issued before any store, which
-  // doubles the memory accesses in flight when the states live in global scratch
-  for (uint32_t g0 = threadIdx.x; g0 < total; g0 += 2 * NT) {
-    cx<R> x[2][4];
-    cx<R> *sp[2];
-    uint32_t o[2][4];
-    const bool two = g0 + NT < total;
+  const uint32_t total = S.packets >> 2;
+  for (uint32_t g = threadIdx.x; g < total; g += NT) {
+    const uint32_t i0 = deposit2(g, lo, hi);
+    const uint32_t o[4] = {bslot(i0), bslot(i0 + mb), bslot(i0 + ma), bslot(i0 + ma + mb)};
+    Pk<R> x[4];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const uint32_t g = h ? (two ? g0 + NT : g0) : g0;
-      const uint32_t j = g >> (n - 2), r = g & (gper - 1u);
-      sp[h] = st + ((size_t)j << n);
-      const uint32_t i0 = deposit2(r, lo, hi);
-      o[h][0] = i0;
-      o[h][1] = i0 + mb;
-      o[h][2] = i0 + ma;
-      o[h][3] = i0 + ma + mb;
+    for (int p = 0; p < 4; ++p) x[p] = S.p[o[p]];
 #pragma unroll
-      for (int p = 0; p < 4; ++p) x[h][p] = sp[h][o[h][p]];
-    }
+    for (int q = 0; q < 4; ++q) {
+      Pk<R> y;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      if (h == 1 && !two) break;
+      for (int e = 0; e < V; ++e) {
+        cx<R> acc = cmake<R>(0, 0);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        cx<R> y = cmake<R>(0, 0);
-#pragma unroll
-        for (int p = 0; p < 4; ++p) cfma(y, m[q * 4 + p], x[h][p]);
-        sp[h][o[h][q]] = y;
+        for (int p = 0; p < 4; ++p) cfma(acc, m[q * 4 + p], x[p].v[e]);
+        y.v[e] = acc;
       }
+      S.p[o[q]] = y;
     }
   }
 }
 
-// Load `rows` FP64 states [rows][N] from global into R precision.
+// B_k <- u^dagger B_{k+1} in place (as apply_states), and acc += a conj(B_k) over the same groups
+// on the way: the environment of the gate on (pa, pb).
 template <typename R, int NT>
-__device__ __forceinline__ void load_states(cx<R> *dst, const c128 *src, int rows, int n) {
-  const uint32_t total = (uint32_t)rows << n;
-  for (uint32_t e = threadIdx.x; e < total; e += NT) {
-    const c128 v = src[e];
-    dst[e] = cmake<R>((R)v.re, (R)v.im);
+__device__ __forceinline__ void unapply_env(BSet<R> B, const Pk<R> *a, int pa, int pb, const cx<R> *u,
+                                            cx<R> (&acc)[16]) {
+  constexpr int V = Pk<R>::V;
+  cx<R> m[16];
+  gate_regs<R>(u, true, m);
+  const int lo = min(pa, pb), hi = max(pa, pb);
+  const uint32_t ma = 1u << pa, mb = 1u << pb;
+  const uint32_t total = B.packets >> 2;
+  for (uint32_t g = threadIdx.x; g < total; g += NT) {
+    const uint32_t i0 = deposit2(g, lo, hi);
+    const uint32_t o[4] = {bslot(i0), bslot(i0 + mb), bslot(i0 + ma), bslot(i0 + ma + mb)};
+    Pk<R> x[4], av[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) x[p] = B.p[o[p]];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) av[p] = a[o[p]];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      Pk<R> y;
+#pragma unroll
+      for (int e = 0; e < V; ++e) {
+        cx<R> t = cmake<R>(0, 0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) cfma(t, m[p * 4 + q], x[q].v[e]);
+        y.v[e] = t;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) cfma_conj(acc[q * 4 + p], av[q].v[e], t);
+      }
+      B.p[o[p]] = y;
+    }
+  }
+}
+
+// Packets of a set's load in flight per thread (the sets come from L2 or memory: one at a time, a
+// set of 8192 amplitudes took 32 round trips of 256 threads).
+constexpr int kSetLoads = 4;
+
+// Packet pk's samples of the FP64 states [rows][N] in global (zero beyond the rows).
+template <typename R>
+__device__ __forceinline__ void fetch_pk(gptr<const c128> src, int rows, int n, uint32_t pk, c128 (&v)[Pk<R>::V]) {
+  const uint32_t i = pk & ((1u << n) - 1u), j = (pk >> n) * Pk<R>::V;
+#pragma unroll
+  for (int e = 0; e < Pk<R>::V; ++e) {
+    const bool in = (int)(j + e) < rows;
+    const gptr<const c128> q = src + (((size_t)(in ? j + e : j) << n) + i);
+    const double re = q->re, im = q->im;
+    v[e] = in ? cmake(re, im) : cmake(0.0, 0.0);
+  }
+}
+
+// The set from FP64 states [rows][N] in global.
+template <typename R, int NT>
+__device__ __forceinline__ void load_states(BSet<R> S, const c128 *src_, int rows, int n) {
+  constexpr int V = Pk<R>::V;
+  const gptr<const c128> src = as_global(src_);
+  for (uint32_t e0 = threadIdx.x; e0 < S.packets; e0 += kSetLoads * NT) {
+    c128 v[kSetLoads][V];
+#pragma unroll
+    for (int i = 0; i < kSetLoads; ++i) fetch_pk<R>(src, rows, n, min(e0 + i * NT, S.packets - 1), v[i]);
+#pragma unroll
+    for (int i = 0; i < kSetLoads; ++i) {
+      Pk<R> y;
+#pragma unroll
+      for (int e = 0; e < V; ++e) y.v[e] = cmake<R>((R)v[i][e].re, (R)v[i][e].im);
+      if (e0 + i * NT < S.packets) S.p[bslot(e0 + i * NT)] = y;
+    }
   }
 }
 
 // (1/rows) sum |x - ref|^2 with ref FP64 in global; every thread gets the result.
 template <typename R, int NT>
-__device__ __forceinline__ double dist_states(const cx<R> *x, const c128 *ref, int rows, int n,
-                                              double *red) {
-  const uint32_t total = (uint32_t)rows << n;
+__device__ __forceinline__ double dist_states(BSet<R> S, const c128 *ref_, int rows, int n, double *red) {
+  constexpr int V = Pk<R>::V;
+  const gptr<const c128> ref = as_global(ref_);
   double acc = 0.0;
-  for (uint32_t e = threadIdx.x; e < total; e += NT) {
-    const c128 r = ref[e];
-    const double dr = (double)x[e].re - r.re, di = (double)x[e].im - r.im;
-    acc += dr * dr + di * di;
+  for (uint32_t e0 = threadIdx.x; e0 < S.packets; e0 += kSetLoads * NT) {
+    c128 v[kSetLoads][V];
+#pragma unroll
+    for (int i = 0; i < kSetLoads; ++i) fetch_pk<R>(ref, rows, n, min(e0 + i * NT, S.packets - 1), v[i]);
+#pragma unroll
+    for (int i = 0; i < kSetLoads; ++i) {
+      if (e0 + i * NT >= S.packets) continue;
+      const Pk<R> x = S.p[bslot(e0 + i * NT)];
+#pragma unroll
+      for (int e = 0; e < V; ++e) {  // (padding samples: zero against zero)
+        const double dr = (double)x.v[e].re - v[i][e].re, di = (double)x.v[e].im - v[i][e].im;
+        acc += dr * dr + di * di;
+      }
+    }
   }
   return block_sum<NT>(acc, red) / (double)rows;
 }
@@ -171,12 +260,18 @@ struct SweepShared {
 constexpr int kGatesInLds = 24;
 
 template <typename R, int NT>
-__device__ void run_job(const BatchArgs &A, int jid, cx<R> *bufA, cx<R> *bufB,
-                        SweepShared<NT / 64> &sh, cx<R> *gl, cx<R> *gates_l) {
+__device__ __forceinline__ void run_job(const BatchArgs &A, int jid, Pk<R> *buf, SweepShared<NT / 64> &sh, cx<R> *gl,
+                                        cx<R> *gates_l) {
   BJob &J = A.jobs[jid];
   BProb &P = A.probs[J.prob];
   const int n = P.n, L = P.L, M = P.M, Mv = P.Mv;
-  const int32_t *pairs = P.pairs;
+  // set A (validation states forward, the backward state), and behind it set B (training states,
+  // B_k); for n >= 4 whole padding blocks, so that A's and B's packets are one run
+  const uint32_t pkA = BSet<R>(buf, max(M, Mv), n).packets;
+  Pk<R> *bufB = buf + bslot((pkA + 15u) & ~15u);
+  const BSet<R> setA(buf, M, n), setB(bufB, M, n), setV(buf, Mv, n), both(buf, 2 * pkA);
+  const bool one_run = Mv == M && n >= 4;
+  const gptr<const int32_t> pairs = as_global(P.pairs), kinds = as_global(P.kinds);
   c128 *g64 = P.g64 + (size_t)J.start * L * 16;
   c128 *vst = P.vst + (size_t)J.start * L * 16;
   const BParams &hp = A.hp;
@@ -201,22 +296,26 @@ __device__ void run_job(const BatchArgs &A, int jid, cx<R> *bufA, cx<R> *bufB,
     __syncthreads();
     return gl;
   };
-  // forward: bufB <- C Psi (training), bufA <- C Psi_val; returns c_val; c0 optional
+  // forward: set B <- C Psi (training), set A <- C Psi_val; returns c_val; c0 optional
   auto forward = [&](double *c0) {
-    load_states<R, NT>(bufB, P.psi, M, n);
-    if (Mv > 0) load_states<R, NT>(bufA, P.psiv, Mv, n);
+    load_states<R, NT>(setB, P.psi, M, n);
+    if (Mv > 0) load_states<R, NT>(setV, P.psiv, Mv, n);
     // the loads fill one element per thread while a gate reads groups of four written by
     // other waves (and gate(k) returns without a barrier when the gates are resident)
     __syncthreads();
     for (int k = 0; k < L; ++k) {
       const cx<R> *u = gate(k);
       const int pa = n - 1 - pairs[2 * k], pb = n - 1 - pairs[2 * k + 1];
-      apply_states<R, NT>(bufB, M, n, pa, pb, u, false);
-      if (Mv > 0) apply_states<R, NT>(bufA, Mv, n, pa, pb, u, false);
+      if (one_run) {
+        apply_states<R, NT>(both, pa, pb, u, false);
+      } else {
+        apply_states<R, NT>(setB, pa, pb, u, false);
+        if (Mv > 0) apply_states<R, NT>(setV, pa, pb, u, false);
+      }
       __syncthreads();
     }
-    if (c0) *c0 = dist_states<R, NT>(bufB, P.phi, M, n, sh.red);
-    return Mv > 0 ? dist_states<R, NT>(bufA, P.phiv, Mv, n, sh.red) : -1.0;
+    if (c0) *c0 = dist_states<R, NT>(setB, P.phi, M, n, sh.red);
+    return Mv > 0 ? dist_states<R, NT>(setV, P.phiv, Mv, n, sh.red) : -1.0;
   };
 
   const int Kmax = A.sweeps_per_launch;
@@ -246,44 +345,29 @@ __device__ void run_job(const BatchArgs &A, int jid, cx<R> *bufA, cx<R> *bufB,
       if (threadIdx.x == 0) J.status = BJ_PAUSED;
       return;
     }
-    // ---- backward (right to left), bufB holds C Psi on entry
-    load_states<R, NT>(bufA, P.phi, M, n);
+    // ---- backward (right to left), set B holds C Psi on entry
+    load_states<R, NT>(setA, P.phi, M, n);
     __syncthreads();
     for (int k = L - 1; k >= 0; --k) {
       const int pa = n - 1 - pairs[2 * k], pb = n - 1 - pairs[2 * k + 1];
-      const int kind = P.kinds ? P.kinds[k] : QFS_GATE_2Q;
+      const int kind = P.kinds ? kinds[k] : QFS_GATE_2Q;
       if (k < L - 1) {
         const cx<R> *u1 = gate(k + 1);  // already updated
         const int qa = n - 1 - pairs[2 * (k + 1)], qb = n - 1 - pairs[2 * (k + 1) + 1];
-        apply_states<R, NT>(bufA, M, n, qa, qb, u1, true);
+        apply_states<R, NT>(setA, qa, qb, u1, true);
         __syncthreads();
       }
       const cx<R> *u0 = gate(k);  // not yet updated
-      apply_states<R, NT>(bufB, M, n, pa, pb, u0, true);  // B_k
-      __syncthreads();
-      if (kind == QFS_GATE_FIXED) continue;  // applied only, no environment
-      // environment of gate k
+      if (kind == QFS_GATE_FIXED) {  // applied only, no environment
+        apply_states<R, NT>(setB, pa, pb, u0, true);  // B_k
+        __syncthreads();
+        continue;
+      }
+      // B_k and the environment of gate k
       cx<R> acc[16];
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[e] = cmake<R>(0, 0);
-      const int lo = min(pa, pb), hi = max(pa, pb);
-      const uint32_t ma = 1u << pa, mb = 1u << pb, gper = 1u << (n - 2);
-      for (uint32_t gi = threadIdx.x; gi < gper * M; gi += NT) {
-        const uint32_t j = gi >> (n - 2), rr = gi & (gper - 1u);
-        const uint32_t i0 = deposit2(rr, lo, hi);
-        const uint32_t o[4] = {i0, i0 + mb, i0 + ma, i0 + ma + mb};
-        const cx<R> *sa = bufA + ((size_t)j << n), *sb = bufB + ((size_t)j << n);
-        cx<R> av[4], bv[4];
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-          av[p] = sa[o[p]];
-          bv[p] = sb[o[p]];
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-          for (int p = 0; p < 4; ++p) cfma_conj(acc[q * 4 + p], av[q], bv[p]);
-      }
+      unapply_env<R, NT>(setB, setA.p, pa, pb, u0, acc);
       const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
       {
         const double ws = bwave_sum_env<R>(acc);
@@ -310,10 +394,10 @@ __device__ void run_job(const BatchArgs &A, int jid, cx<R> *bufA, cx<R> *bufB,
     // cost of the updated gates: a_0 = u_0^dag a
     {
       const int pa = n - 1 - pairs[0], pb = n - 1 - pairs[1];
-      apply_states<R, NT>(bufA, M, n, pa, pb, resident ? gates_l : gl, true);  // the new u_0
+      apply_states<R, NT>(setA, pa, pb, resident ? gates_l : gl, true);  // the new u_0
       __syncthreads();
     }
-    const double ct = dist_states<R, NT>(bufA, P.psi, M, n, sh.red);
+    const double ct = dist_states<R, NT>(setA, P.psi, M, n, sh.red);
     __syncthreads();
     cval = forward(nullptr);
     // ---- control (App. A), one thread
@@ -352,14 +436,15 @@ __device__ void run_job(const BatchArgs &A, int jid, cx<R> *bufA, cx<R> *bufB,
   }
 }
 
-template <typename R, int NT>
+// SCR: the sets in this work-group's global slot instead of LDS (an instantiation of its own, so
+// that either kind is accessed by its own instructions).
+template <typename R, int NT, bool SCR>
 __global__ __launch_bounds__(NT) void k_batch_sweep(BatchArgs A) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   __shared__ SweepShared<NT / 64> sh;
   __shared__ int qi_s;
   __shared__ __align__(16) cx<R> gl[16];
   __shared__ __align__(16) cx<R> gates_l[kGatesInLds * 16];
-  cx<R> *lds = reinterpret_cast<cx<R> *>(lds_raw);
   for (;;) {
     if (threadIdx.x == 0) qi_s = atomicAdd(A.queue_head, 1);
     __syncthreads();
@@ -367,19 +452,11 @@ __global__ __launch_bounds__(NT) void k_batch_sweep(BatchArgs A) {
     __syncthreads();
     if (qi >= A.njobs) break;
     const int jid = A.queue[qi];
-    const BProb &P = A.probs[A.jobs[jid].prob];
-    const size_t rowsA = (size_t)max(P.M, P.Mv) << P.n, rowsB = (size_t)P.M << P.n;
-    cx<R> *bufA, *bufB;
-    if (A.scratch) {  // states in this work-group's global slot
-      cx<R> *slot = reinterpret_cast<cx<R> *>(A.scratch + (size_t)blockIdx.x * A.scratch_slot_bytes);
-      bufA = slot;
-      bufB = slot + rowsA;
-    } else {
-      bufA = lds;
-      bufB = lds + rowsA;
-    }
-    (void)rowsB;
-    run_job<R, NT>(A, jid, bufA, bufB, sh, gl, gates_l);
+    if constexpr (SCR)
+      run_job<R, NT>(A, jid, reinterpret_cast<Pk<R> *>(A.scratch + (size_t)blockIdx.x * A.scratch_slot_bytes), sh, gl,
+                     gates_l);
+    else
+      run_job<R, NT>(A, jid, reinterpret_cast<Pk<R> *>(lds_raw), sh, gl, gates_l);
     __syncthreads();
   }
 }
@@ -643,8 +720,12 @@ int launch_batch_gates(BProb *probs_dev, const int32_t *prob_of, const int32_t *
 template <typename R, int NT>
 static int launch_sweep_t(const BatchArgs &a, int grid, size_t lds, hipStream_t s) {
   static size_t attr = 0;
-  QFS_TRY(ensure_dynamic_lds(reinterpret_cast<const void *>(&k_batch_sweep<R, NT>), lds, &attr));
-  hipLaunchKernelGGL((k_batch_sweep<R, NT>), dim3(grid), dim3(NT), lds, s, a);
+  if (a.scratch) {
+    hipLaunchKernelGGL((k_batch_sweep<R, NT, true>), dim3(grid), dim3(NT), 0, s, a);
+  } else {
+    QFS_TRY(ensure_dynamic_lds(reinterpret_cast<const void *>(&k_batch_sweep<R, NT, false>), lds, &attr));
+    hipLaunchKernelGGL((k_batch_sweep<R, NT, false>), dim3(grid), dim3(NT), lds, s, a);
+  }
   QFS_HIP(hipGetLastError());
   return QFS_OK;
 }

@@ -374,8 +374,7 @@ int qfs::batch_instantiate(int32_t P, const qfs_template *tmpl, const qfs_target
       const BJob &J = jobs[j];
       if (finished[J.prob] || J.status != BJ_RUN) continue;
       const BProb &d = hp[J.prob];
-      const size_t cb = J.fp64 ? sizeof(c128) : sizeof(c64);
-      const size_t bytes = ((size_t)std::max(d.M, d.Mv) + d.M) * ((size_t)1 << d.n) * cb;
+      const size_t bytes = batch_set_bytes(d.M, d.Mv, d.n, J.fp64 != 0);
       classes[ClassKey{J.fp64, pow2_at_least(bytes, 4096)}].push_back((int32_t)j);
     }
     if (classes.empty()) break;
@@ -388,7 +387,7 @@ int qfs::batch_instantiate(int32_t P, const qfs_template *tmpl, const qfs_target
     // Size classes are launched concurrently on side streams (each with its own queue
     // segment, queue head and scratch region); a class whose work-group size is not
     // known yet is first autotuned on the call's stream: its jobs are dealt to three
-    // parts run with 64, 128 and 256 threads, one after the other.
+    // parts run with three work-group sizes, one after the other.
     struct Launch {
       ClassKey key;
       int threads, grid, nj;
@@ -408,7 +407,7 @@ int qfs::batch_instantiate(int32_t P, const qfs_template *tmpl, const qfs_target
       });
       const ClassKey key = kv.first;
       const bool use_lds = key.bucket <= kLdsLimit;
-      const size_t lds = use_lds ? key.bucket : 0;
+      const size_t lds = use_lds ? batch_padded_bytes(key.bucket) : 0;
       int chosen = p.batch_threads;
       if (!chosen && !use_lds) chosen = 512;  // global-scratch states: wider groups
       if (!chosen) {
@@ -418,10 +417,12 @@ int qfs::batch_instantiate(int32_t P, const qfs_template *tmpl, const qfs_target
       }
       if (!chosen && ids.size() >= 3 * 64) {
         // autotune on the call's stream: the class's jobs (longest first) dealt round robin
-        // to three parts of like size mix, run with 64, 128 and 256 threads one after the
+        // to three parts of like size mix, run with three work-group sizes one after the
         // other; a part's rate is the work its jobs did in the launch (their own work
         // counters, so jobs that stop early count what they ran) per millisecond
-        const int cands[3] = {64, 128, 256};
+        // (sets above 48 KB leave room for two or fewer work-groups per compute unit: wider ones)
+        const bool large = lds > 48 * 1024;
+        const int cands[3] = {large ? 128 : 64, large ? 256 : 128, large ? 512 : 256};
         std::vector<int32_t> part_ids[3];
         for (size_t q = 0; q < ids.size(); ++q) part_ids[q % 3].push_back(ids[q]);
         float part_ms[3] = {0.f, 0.f, 0.f};
@@ -479,7 +480,7 @@ int qfs::batch_instantiate(int32_t P, const qfs_template *tmpl, const qfs_target
       qhost.insert(qhost.end(), ids.begin(), ids.end());
       qfill += ids.size();
       l.soff = sfill;
-      if (!use_lds) sfill += (size_t)l.grid * key.bucket;
+      if (!use_lds) sfill += (size_t)l.grid * batch_padded_bytes(key.bucket);
       plan.push_back(l);
     }
     if (!plan.empty()) {
@@ -503,8 +504,8 @@ int qfs::batch_instantiate(int32_t P, const qfs_template *tmpl, const qfs_target
         a.hp = bp;
         const bool use_lds = l.key.bucket <= kLdsLimit;
         a.scratch = use_lds ? nullptr : scratch.as<char>() + l.soff;
-        a.scratch_slot_bytes = use_lds ? 0 : l.key.bucket;
-        QFS_TRY(launch_batch_sweep(a, l.key.fp64 != 0, l.threads, l.grid, use_lds ? l.key.bucket : 0,
+        a.scratch_slot_bytes = use_lds ? 0 : batch_padded_bytes(l.key.bucket);
+        QFS_TRY(launch_batch_sweep(a, l.key.fp64 != 0, l.threads, l.grid, use_lds ? batch_padded_bytes(l.key.bucket) : 0,
                                    side[c % ns]));
         if (batch_trace())
           std::fprintf(stderr, "qfs batch: K=%d fp64=%d state_bytes<=%zu threads=%d jobs=%d grid=%d\n", K,
