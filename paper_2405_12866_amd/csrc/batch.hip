@@ -17,6 +17,7 @@
 #include "polar2.h"
 #include "polar4.h"
 #include "stream_common.h"
+#include "wave_sums.h"
 
 namespace qfs {
 
@@ -35,38 +36,6 @@ __device__ __forceinline__ R bwave_sum(R x) {
 __device__ __forceinline__ uint32_t deposit2(uint32_t r, int lo, int hi) {
   r += r & ~((1u << lo) - 1u);
   return r + (r & ~((1u << hi) - 1u));
-}
-
-// Wave sums of the 16 complex entries of a 4x4 environment (32 reals, FP64) by recursive
-// halving: at the exchange with lane ^ 2C each lane keeps half of its values (the upper
-// half when that lane bit is set) and adds its partner's copy of that half; a last
-// exchange with lane ^ 1 completes the sums. Lane l returns the wave sum of real value
-// l >> 1 (value 2e is entry e's real part, 2e + 1 its imaginary part).
-template <int C>
-__device__ __forceinline__ void bhalve(double (&v)[32], int lane) {
-  const bool hi = (lane & (2 * C)) != 0;
-#pragma unroll
-  for (int i = 0; i < C; ++i) {
-    const double give = hi ? v[i] : v[C + i];
-    const double keep = hi ? v[C + i] : v[i];
-    v[i] = keep + __shfl_xor(give, 2 * C);
-  }
-}
-template <typename R>
-__device__ __forceinline__ double bwave_sum_env(const cx<R> (&acc)[16]) {
-  const int lane = threadIdx.x & 63;
-  double v[32];
-#pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    v[2 * e] = (double)acc[e].re;
-    v[2 * e + 1] = (double)acc[e].im;
-  }
-  bhalve<16>(v, lane);
-  bhalve<8>(v, lane);
-  bhalve<4>(v, lane);
-  bhalve<2>(v, lane);
-  bhalve<1>(v, lane);
-  return v[0] + __shfl_xor(v[0], 1);
 }
 
 // Sum over the work-group; result valid in every thread. `red` holds NT/64 values.
@@ -370,9 +339,15 @@ __device__ __forceinline__ void run_job(const BatchArgs &A, int jid, Pk<R> *buf,
       unapply_env<R, NT>(setB, setA.p, pa, pb, u0, acc);
       const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
       {
-        const double ws = bwave_sum_env<R>(acc);
-        // (value 2e + part lands on the real or imaginary half of entry e)
-        if ((lane & 1) == 0) reinterpret_cast<double *>(&sh.wred[w][0])[lane >> 1] = ws;
+        // value 2e of entry e's real part, 2e + 1 of its imaginary part
+        double v[32];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          v[2 * e] = (double)acc[e].re;
+          v[2 * e + 1] = (double)acc[e].im;
+        }
+        const double ws = wave_sums<double, 32>(v);
+        if (lane < 32) reinterpret_cast<double *>(&sh.wred[w][0])[wave_sums_index<32>(lane)] = ws;
       }
       __syncthreads();
       if (threadIdx.x < 16) {

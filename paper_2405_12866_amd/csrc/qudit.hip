@@ -21,6 +21,7 @@
 #include "philox.h"
 #include "polar4.h"
 #include "qfs_internal.h"
+#include "wave_sums.h"
 
 namespace qfs {
 namespace {
@@ -158,35 +159,6 @@ __global__ __launch_bounds__(kQdBlock) void k_qd_apply(QdSeg<R> s0, QdSeg<R> s1,
   }
 }
 
-// Wave sums of NV values (NV = 16, 32 or 64; FP64) by recursive halving: at the exchange
-// with lane ^ MASK each lane keeps C of its 2C values (the upper ones when that lane bit is
-// set) and adds its partner's copy; the lane bits left over are summed plainly. Lane l
-// returns the wave sum of value l >> (6 - log2 NV).
-template <int C, int MASK, int NV>
-__device__ __forceinline__ void qhalve(double (&v)[NV], int lane) {
-  const bool hi = (lane & MASK) != 0;
-#pragma unroll
-  for (int i = 0; i < C; ++i) {
-    const double give = hi ? v[i] : v[C + i];
-    const double keep = hi ? v[C + i] : v[i];
-    v[i] = keep + __shfl_xor(give, MASK);
-  }
-}
-template <int NV>
-__device__ __forceinline__ double qwave_sum(double (&v)[NV]) {
-  static_assert(NV == 16 || NV == 32 || NV == 64, "16, 32 or 64 values");
-  const int lane = threadIdx.x & 63;
-  qhalve<NV / 2, 32>(v, lane);
-  qhalve<NV / 4, 16>(v, lane);
-  qhalve<NV / 8, 8>(v, lane);
-  qhalve<NV / 16, 4>(v, lane);
-  if constexpr (NV >= 32) qhalve<NV / 32, 2>(v, lane);
-  else v[0] += __shfl_xor(v[0], 2);
-  if constexpr (NV >= 64) qhalve<1, 1>(v, lane);
-  else v[0] += __shfl_xor(v[0], 1);
-  return v[0];
-}
-
 // Rows of the environment one block accumulates: d (one value of the first gate qudit's
 // digit) for d <= 3, two for d = 4, where d rows would hold 128 FP64 accumulators a thread.
 template <int d>
@@ -254,10 +226,9 @@ __global__ __launch_bounds__(kQdBlock) void k_qd_env(const cx<R> *a, int64_t a_s
       }
 #pragma unroll
     for (int i = NR; i < NV; ++i) v[i] = 0.0;
-    const double ws = qwave_sum<NV>(v);
-    constexpr int SH = NV == 16 ? 2 : (NV == 32 ? 1 : 0);
-    const int idx = lane >> SH;
-    if ((lane & ((1 << SH) - 1)) == 0 && idx < NR) reinterpret_cast<double *>(&red[w][0])[idx] = ws;
+    const double ws = wave_sums<double, NV>(v);
+    const int idx = wave_sums_index<NV>(lane);
+    if (lane < NV && idx < NR) reinterpret_cast<double *>(&red[w][0])[idx] = ws;
   }
   __syncthreads();
   if (threadIdx.x < RY * D) {

@@ -22,6 +22,7 @@
 #include "polar2.h"
 #include "polar4.h"
 #include "stream_common.h"
+#include "wave_sums.h"
 #include "qfs_internal.h"
 
 namespace qfs {
@@ -39,24 +40,10 @@ __device__ __forceinline__ R wave_sum(R x) {
   return x;
 }
 
-// Wave sums of the 16 complex entries of a 4x4 environment (32 reals) by recursive
-// halving: at the exchange with lane ^ m (m = 32 .. 2) each lane keeps half of its values
-// (the upper half when its bit m is set) and adds its partner's copy of that half, so 31
-// exchanges replace 6 per value; a last exchange with lane ^ 1 completes the sums. Lane l
-// returns the wave sum of real value l >> 1 (entry (l >> 2), real part when bit 1 of l is
-// clear).
-template <int C, typename R>
-__device__ __forceinline__ void halve_level(R (&v)[32], int lane) {
-  const bool hi = (lane & (2 * C)) != 0;
-#pragma unroll
-  for (int i = 0; i < C; ++i) {
-    const R give = hi ? v[i] : v[C + i];
-    const R keep = hi ? v[C + i] : v[i];
-    v[i] = keep + __shfl_xor(give, 2 * C);
-  }
-}
+// Wave sums of the 16 complex entries of a 4x4 environment (value 2e: entry e's real part,
+// 2e + 1 its imaginary part) into red[0 .. 31].
 template <typename R>
-__device__ __forceinline__ R wave_sum_env(const cx<R> (&acc)[16]) {
+__device__ __forceinline__ void wave_sum_env(const cx<R> (&acc)[16], double *red) {
   const int lane = threadIdx.x & 63;
   R v[32];
 #pragma unroll
@@ -64,12 +51,8 @@ __device__ __forceinline__ R wave_sum_env(const cx<R> (&acc)[16]) {
     v[2 * e] = acc[e].re;
     v[2 * e + 1] = acc[e].im;
   }
-  halve_level<16>(v, lane);
-  halve_level<8>(v, lane);
-  halve_level<4>(v, lane);
-  halve_level<2>(v, lane);
-  halve_level<1>(v, lane);
-  return v[0] + __shfl_xor(v[0], 1);
+  const R ws = wave_sums<R, 32>(v);
+  if (lane < 32) red[wave_sums_index<32>(lane)] = (double)ws;
 }
 
 // Local index of the environment gate's (q, sigma) inside a super group, per variant
@@ -607,8 +590,7 @@ __global__ __launch_bounds__(kBlock) void k_bwd_step(StepArgs<R> A) {
 
   // thread -> wave -> block partial (FP64 across waves)
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const R ws = wave_sum_env<R>(acc);
-  if ((lane & 1) == 0) red[wv][lane >> 1] = (double)ws;
+  wave_sum_env<R>(acc, red[wv]);
   __syncthreads();
   if (threadIdx.x < 16) {
     const int e = threadIdx.x;
@@ -765,8 +747,7 @@ __global__ __launch_bounds__(kLdsBlock) void k_bwd_step_lds(StepArgs<R> A, LdsGe
     wave_sync();
   }
 
-  const R ws = wave_sum_env<R>(acc);
-  if ((lane & 1) == 0) red[wv][lane >> 1] = (double)ws;
+  wave_sum_env<R>(acc, red[wv]);
   __syncthreads();
   if (threadIdx.x < 16) {
     const int e = threadIdx.x;
