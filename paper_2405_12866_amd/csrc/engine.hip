@@ -786,7 +786,7 @@ int sweep_backward(SweepCtx &c) {
                                  hn[h], c.partials, &P, hs[h], k_apply2));
       QFS_TRY(T.end(hs[h], kClsStep, (k_apply < 0 ? 2.0 : 3.0) * set_bytes<R>(c, c.g) * hn[h] / c.nslots));
       QFS_TRY(T.begin(hs[h]));
-      QFS_TRY(launch_env_finalize(P, c.partials, hslots[h], hn[h], nullptr, true, c.beta, c.g64,
+      QFS_TRY(launch_env_finalize(P, c.partials, hslots[h], hn[h], c.beta, c.g64,
                                   sizeof(R) == 4 ? c.g32 : nullptr, c.L * 16, k, c.vstore, kind, hs[h]));
       QFS_TRY(T.end(hs[h], kClsPolar, (double)P * 256.0 * hn[h]));
     }
@@ -1992,32 +1992,6 @@ int qfs_dense_apply(int32_t n, int32_t M, const qfs_c128 *U, const qfs_c128 *psi
   }
   QFS_TRY(launch_dense_rows(N, M, reinterpret_cast<const c128 *>(U), reinterpret_cast<const c128 *>(psi), dst, s));
   if (tmp.ptr) QFS_HIP(hipMemcpyAsync(out, dst, sizeof(c128) * M * N, hipMemcpyDeviceToDevice, s));
-  return scope.done(s);
-}
-
-int qfs_environment(int32_t n, int32_t M, const qfs_c128 *a, const qfs_c128 *b, int32_t qa,
-                    int32_t qb, qfs_c128 *gamma, void *hip_stream) {
-  const int32_t pr[2] = {qa, qb};
-  qfs_template t{n, 1, pr};
-  QFS_TRY(validate_template(&t));
-  if (M < 1 || !a || !b || !gamma) return QFS_EINVAL;
-  hipStream_t s = as_stream(hip_stream);
-  BufferScope scope;
-  const Geometry g = api_geometry(n, M);
-  DevBuf A, B, slot, part;
-  QFS_TRY(A.alloc(sizeof(c128) * g.elems()));
-  QFS_TRY(B.alloc(sizeof(c128) * g.elems()));
-  QFS_TRY(part.alloc(sizeof(c128) * 16 * kPcap));
-  QFS_TRY(one_slot(slot, s));
-  QFS_TRY(launch_to_internal<double>(n, M, g.logC, g.nch, reinterpret_cast<const c128 *>(a), A.as<c128>(), s));
-  QFS_TRY(launch_to_internal<double>(n, M, g.logC, g.nch, reinterpret_cast<const c128 *>(b), B.as<c128>(), s));
-  GateRef gr{nullptr, nullptr, 0};
-  int P = 0;
-  QFS_TRY(launch_bwd_step<double>(g, pr, -1, 0, gr, SBuf<double>{A.as<c128>(), 0},
-                                  SBuf<double>{A.as<c128>(), 0}, SBuf<double>{B.as<c128>(), 0},
-                                  slot.as<int32_t>(), 1, part.as<c128>(), &P, s));
-  QFS_TRY(launch_env_finalize(P, part.as<c128>(), slot.as<int32_t>(), 1, reinterpret_cast<c128 *>(gamma),
-                              false, 0.0, nullptr, nullptr, 0, 0, nullptr, QFS_GATE_2Q, s));
   return scope.done(s);
 }
 

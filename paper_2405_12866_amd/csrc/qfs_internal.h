@@ -371,8 +371,7 @@ int launch_pack(const Geometry &g, int64_t ld, const c128 *master, cx<R> *dst, h
 // per-block FP64 partial sums
 // [S][kPcap][16] (blocks 0 .. P-1 of each start; P returned). launch_env_finalize (one
 // wave per start) reduces them in a fixed order and writes u_s[k_env] <- polar((1-beta) Gamma + beta u) to both gate
-// copies (kind QFS_GATE_1Q: the one-qubit update of a v (x) I_2 slot); optionally stores
-// Gamma (FP64) to gamma_out[s].
+// copies (kind QFS_GATE_1Q: the one-qubit update of a v (x) I_2 slot).
 template <typename R>
 int launch_bwd_step(const Geometry &g, const int32_t *pairs_host, int k_apply, int k_env,
                     GateRef gates, SBuf<R> a_in, SBuf<R> a_out, SBuf<R> b,
@@ -381,7 +380,7 @@ int launch_bwd_step(const Geometry &g, const int32_t *pairs_host, int k_apply, i
 // vstore (nullable, [S][L][16]): right singular vectors of each gate's last update,
 // used to warm-start the Jacobi iteration and updated in place.
 int launch_env_finalize(int P, const c128 *partials, const int32_t *slot_to_start, int nslots,
-                        c128 *gamma_out, bool do_update, double beta, c128 *g64, c64 *g32,
+                        double beta, c128 *g64, c64 *g32,
                         int32_t gstride, int32_t k_env, c128 *vstore, int kind, hipStream_t s);
 // count 4x4 identity matrices.
 int launch_identity4(int64_t count, c128 *v, hipStream_t s);

@@ -766,7 +766,6 @@ constexpr int kFinBlock = 256;
 
 __global__ __launch_bounds__(kFinBlock) void k_env_finalize(const c128 *partials, int P,
                                                             const int32_t *slot_to_start,
-                                                            c128 *gamma_out, int do_update,
                                                             double beta, c128 *g64, c64 *g32,
                                                             int32_t gstride, int32_t k_env,
                                                             c128 *vstore, int kind) {
@@ -793,10 +792,9 @@ __global__ __launch_bounds__(kFinBlock) void k_env_finalize(const c128 *partials
     c128 tot = gsum[0][e];
     for (int g = 1; g < G; ++g) tot = tot + gsum[g][e];
     gam[e] = tot;
-    if (gamma_out) gamma_out[(int64_t)s * 16 + e] = tot;
   }
   __syncthreads();
-  if (do_update && threadIdx.x < 64) {
+  if (threadIdx.x < 64) {
     c128 *u64 = g64 + (int64_t)s * gstride + k_env * 16;
     c64 *u32 = g32 ? g32 + (int64_t)s * gstride + k_env * 16 : nullptr;
     if (kind == QFS_GATE_1Q) {
@@ -1248,11 +1246,11 @@ int launch_bwd_step(const Geometry &g, const int32_t *pairs_host, int k_apply, i
 }
 
 int launch_env_finalize(int P, const c128 *partials, const int32_t *slot_to_start, int nslots,
-                        c128 *gamma_out, bool do_update, double beta, c128 *g64, c64 *g32,
+                        double beta, c128 *g64, c64 *g32,
                         int32_t gstride, int32_t k_env, c128 *vstore, int kind, hipStream_t s) {
   if (nslots <= 0) return QFS_OK;
   hipLaunchKernelGGL(k_env_finalize, dim3(nslots), dim3(kFinBlock), 0, s, partials, P, slot_to_start,
-                     gamma_out, do_update ? 1 : 0, beta, g64, g32, gstride, k_env, vstore, kind);
+                     beta, g64, g32, gstride, k_env, vstore, kind);
   QFS_HIP(hipGetLastError());
   return QFS_OK;
 }
