@@ -99,17 +99,28 @@ struct GroupArgs {
   int32_t tpos[kMaxBits];  // chunk-local position of tile bit i (ascending)
   int32_t xpos[kMaxBits];  // chunk-local positions outside the tile (ascending)
   int32_t apos[4];         // tile packet-bit positions of the operator's four slots
-  int32_t cpos[kMaxBits];  // the other tile packet bits (ascending): the operator's columns
+  uint32_t amask[4];       // ~(2^p - 1) of those positions, ascending
   int32_t env;             // reduce the second-moment matrix
   int32_t zpos[4];         // tile packet-bit positions of the four slots of the reduction
-  int32_t nK;              // packet bits of the reduction index
-  int32_t kpos[kMaxBits];  // their tile packet-bit positions (ascending)
+  uint32_t zmask[4];       // ~(2^p - 1) of those positions, ascending
+  int32_t nK;              // packet bits of the reduction index: the other ones
 };
 
 __device__ __forceinline__ uint32_t spread_bits(uint32_t x, const int32_t *pos, int nb) {
   uint32_t r = 0;
   for (int i = 0; i < nb; ++i) r |= ((x >> i) & 1u) << pos[i];
   return r;
+}
+
+// x with zero bits put in at four ascending positions (masks ~(2^p - 1)): the bits from a
+// position on move up by one when that part is added once more. Eight instructions and no
+// loads, where spreading x over a list of positions took a scalar load and its latency per bit,
+// in every block of columns and step of the reduction: with it the pass of half of 16 starts
+// (12 qubits, M = 256, beside the other half's) takes 62 us, 69 before.
+__device__ __forceinline__ uint32_t insert4(uint32_t x, const uint32_t (&m)[4]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) x += x & m[i];
+  return x;
 }
 
 __device__ __forceinline__ int lds_slot16(uint32_t pk) { return (int)(pk + (pk >> 4)); }
@@ -141,9 +152,11 @@ constexpr int kMaxPkt = 2048 / kGBlock;
 
 // DIST selects the distance pass (the last group's operator applied to the state, then
 // sum |a - b|^2) instead of the environment pass; each has its own kernel, so neither
-// carries the other's registers.
+// carries the other's registers. Four waves a SIMD: the FP64 pass then spills ten registers
+// outside its tile loop's products, and takes 23.3 us (11 qubits, M = 100, 5 starts) instead
+// of the 24.5 of three waves; the FP32 one needs no more than 116 anyway.
 template <typename R, bool DIST>
-__global__ __launch_bounds__(kGBlock) void k_bwd_group(GroupArgs<R> A) {
+__global__ __launch_bounds__(kGBlock, 4) void k_bwd_group(GroupArgs<R> A) {
   constexpr int V = Pk<R>::V, LOGV = Pk<R>::LOGV;
   using MF = Mfma<R>;
   using acc_t = typename MF::acc_t;
@@ -162,7 +175,7 @@ __global__ __launch_bounds__(kGBlock) void k_bwd_group(GroupArgs<R> A) {
   const cx<R> *bsrc = A.b + A.b_stride * s;
   const int n = A.n, logC = A.logC, nX = A.nX;
 
-  // chunk-local element offset of packet tid + 256 u of a tile: the bits are disjoint, so
+  // chunk-local element offset of packet tid + kGBlock u of a tile: the bits are disjoint, so
   // the offset of the thread's bits and of u's bits are ORed
   const uint32_t lowmask = (1u << A.lowP) - 1u;
   const int nhi = nP - A.lowP;
@@ -212,9 +225,6 @@ __global__ __launch_bounds__(kGBlock) void k_bwd_group(GroupArgs<R> A) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) zoff |= (uint32_t)((zl >> i) & 1) << A.zpos[i];
   const int nK = A.nK;
-  uint32_t kkoff = 0;
-  if (nK >= 1) kkoff |= (uint32_t)(kk & 1) << A.kpos[0];
-  if (nK >= 2) kkoff |= (uint32_t)((kk >> 1) & 1) << A.kpos[1];
   const bool kk_ok = kk < (1 << min(nK, 2));
   const uint32_t nkq = nK >= 2 ? 1u << (nK - 2) : 1u;
   double gre[4] = {0.0, 0.0, 0.0, 0.0}, gim[4] = {0.0, 0.0, 0.0, 0.0};
@@ -267,7 +277,7 @@ __global__ __launch_bounds__(kGBlock) void k_bwd_group(GroupArgs<R> A) {
         const uint32_t j = blk * 16 + (lane & 15);
         const bool ok = j < ncols;
         const int e = (int)(j & (V - 1));
-        const uint32_t cofs = spread_bits(j >> LOGV, A.cpos, ncb);
+        const uint32_t cofs = insert4(j >> LOGV, A.amask);
         acc_t t1 = {0, 0, 0, 0}, t2 = {0, 0, 0, 0}, t3 = {0, 0, 0, 0};
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
@@ -296,7 +306,7 @@ __global__ __launch_bounds__(kGBlock) void k_bwd_group(GroupArgs<R> A) {
       // T2 = Re a Im b^T, T3 = Im a Re b^T; Re G = T1 - T2 - T3, Im G = T3 - T2
       acc_t t1 = {0, 0, 0, 0}, t2 = {0, 0, 0, 0}, t3 = {0, 0, 0, 0};
       for (uint32_t j = wv; j < nkq; j += kGWaves) {
-        const uint32_t pk = zoff | kkoff | (nK > 2 ? spread_bits(j, A.kpos + 2, nK - 2) : 0u);
+        const uint32_t pk = zoff | insert4((j << 2) | (kk_ok ? kk : 0), A.zmask);
         Pk<R> av, bv;
         if (kk_ok) {
           av = lds_pk<R>(la, pk);
@@ -933,19 +943,21 @@ int launch_group_pass(const Geometry &g, const int32_t *pairs, const GateGroup *
       used[p] = true;
     }
   };
+  auto masks = [&](const bool (&used)[kMaxBits], uint32_t (&m)[4]) {
+    for (int p = 0, c = 0; p < nP; ++p)
+      if (used[p]) m[c++] = ~((1u << p) - 1u);
+  };
   if (prev) {
     bool used[kMaxBits] = {};
     slots4(*prev, A.apos, used);
-    for (int p = 0, c = 0; p < nP; ++p)
-      if (!used[p]) A.cpos[c++] = p;
+    masks(used, A.amask);
   }
   A.env = (!dist && cur && cur->nvar > 0) ? 1 : 0;
   if (A.env) {
     bool used[kMaxBits] = {};
     slots4(*cur, A.zpos, used);
-    A.nK = 0;
-    for (int p = 0; p < nP; ++p)
-      if (!used[p]) A.kpos[A.nK++] = p;
+    masks(used, A.zmask);
+    A.nK = nP - 4;
   }
   const uint32_t npk = 1u << (A.nT - LOGV);
   const size_t lds = std::max<size_t>(2 * (size_t)(npk + (npk >> 4)) * 16, (size_t)kGWaves * 256 * 16);
