@@ -228,7 +228,8 @@ static void *pinned_take(size_t bytes) {
     }
   }
   void *p = nullptr;
-  if (hipHostMalloc(&p, bytes) != hipSuccess) {
+  // (coherent: kernels write costs into it)
+  if (hipHostMalloc(&p, bytes, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
     (void)hipGetLastError();
     return nullptr;
   }
@@ -472,6 +473,9 @@ struct SweepCtx {
   c128 *partials = nullptr;  // [S][kPcap][16]
   double *dpart0 = nullptr, *dpart1 = nullptr;  // [S][kPcap] each
   double *costs = nullptr;   // [3 S]: c_train, c_val, c_0
+  // set: the sweep leaves its costs' block sums to the launch that ends it, and notes here how
+  // many there are of each start
+  SweepEnd *end = nullptr;
   int S = 0;
   KernelTimer *timer = nullptr;
   hipStream_t stream = nullptr;
@@ -501,6 +505,19 @@ struct SweepCtx {
   hipStream_t pstream[kParts] = {};
   hipEvent_t pfork = nullptr, pjoin[kParts] = {};
 };
+
+// The training (which = 0) or validation cost from its n block sums per start, taken now or
+// left to the end of the sweep.
+int dist_end(SweepCtx &c, int which, int n, int stride, const int32_t *slots, int nslots, hipStream_t s) {
+  const double *part = which ? c.dpart1 : c.dpart0;
+  const int m = which ? c.gv.M : c.g.M;
+  if (!c.end) return launch_dist_finalize(n, part, slots, nslots, m, c.costs + which * c.S, s, stride);
+  c.end->part[which] = part;
+  c.end->n[which] = n;
+  c.end->stride[which] = stride;
+  c.end->m[which] = (double)m;
+  return QFS_OK;
+}
 
 template <typename R>
 GateRef gate_ref(const SweepCtx &c) {
@@ -556,7 +573,7 @@ int sweep_forward(SweepCtx &c, bool with_c0) {
     const double bytes = set_bytes<R>(c, c.g) * (1 + stored + (with_c0 ? 1 : 0)) +
                          (val ? 2.0 * set_bytes<R>(c, c.gv) : 0.0);
     QFS_TRY(T.end(c.stream, kClsForward, bytes));
-    if (val) QFS_TRY(launch_dist_finalize(c.gv.nch, c.dpart1, c.slots, c.nslots, c.gv.M, c.costs + c.S, c.stream));
+    if (val) QFS_TRY(dist_end(c, 1, c.gv.nch, c.gv.nch, c.slots, c.nslots, c.stream));
     if (with_c0)
       QFS_TRY(launch_dist_finalize(c.g.nch, c.dpart0, c.slots, c.nslots, c.g.M, c.costs + 2 * c.S, c.stream));
     return QFS_OK;
@@ -586,7 +603,7 @@ int sweep_forward(SweepCtx &c, bool with_c0) {
                                  c.L == 1 ? SBuf<R>{psiv, 0} : SBuf<R>{Vs, vstride}, SBuf<R>{phiv, 0},
                                  c.slots, c.nslots, c.dpart1, &P, c.stream));
     QFS_TRY(T.end(c.stream, kClsDist, 2.0 * set_bytes<R>(c, c.gv)));
-    QFS_TRY(launch_dist_finalize(P, c.dpart1, c.slots, c.nslots, c.gv.M, c.costs + c.S, c.stream));
+    QFS_TRY(dist_end(c, 1, P, P, c.slots, c.nslots, c.stream));
   }
   if (with_c0) {
     QFS_TRY(T.begin(c.stream));
@@ -648,7 +665,7 @@ int grouped_item(SweepCtx &c, const int32_t *slots, int n, hipStream_t st, int i
                                  SBuf<R>{psi, 0}, slots, n, group_blocks_per_start(c.nslots), nullptr, kGPcap,
                                  c.dpart0, &P, st, le));
     QFS_TRY(T.ext_end(kClsDist, 2.0 * set));
-    return launch_dist_finalize(P, c.dpart0, slots, n, c.g.M, c.costs, st, kGPcap);
+    return dist_end(c, 0, P, kGPcap, slots, n, st);
   }
   SweepCtx sub = c;
   sub.slots = slots;
@@ -802,8 +819,7 @@ int sweep_backward(SweepCtx &c) {
                                a_written ? SBuf<R>{A, sN} : SBuf<R>{phi, 0}, SBuf<R>{psi, 0}, c.slots,
                                c.nslots, c.dpart0, &P, c.stream));
   QFS_TRY(T.end(c.stream, kClsDist, 2.0 * set_bytes<R>(c, c.g)));
-  QFS_TRY(launch_dist_finalize(P, c.dpart0, c.slots, c.nslots, c.g.M, c.costs, c.stream));
-  return QFS_OK;
+  return dist_end(c, 0, P, P, c.slots, c.nslots, c.stream);
 }
 
 // ------------------------------------------------------------------ control loop
@@ -910,6 +926,7 @@ class Group {
   // sweep parity and part, written on the part's stream right after its sweep
   double *h_costs_ = nullptr;
   size_t h_costs_bytes_ = 0;
+  SweepEnd end_;  // of the last sweep issued (a graph's counts hold for its replays)
   double *cost_buf(int par, int part) { return h_costs_ + (size_t)(1 + par * SweepCtx::kParts + part) * 3 * S_; }
   // The control loop's sweeps: run-ahead (spec_), per sweep parity the starts and parts it
   // was issued with and an event per part at its end (timing reference seg0_), and the
@@ -1213,25 +1230,33 @@ int Group::end_segment() {
 
 // One sweep of the running starts (parity par). A grouped sweep without timing or graphs
 // runs its parts on their streams with no join, each part going on into its next sweep;
-// after each part: the snapshot of its gates (run-ahead only), its costs to the host and
-// its end event.
+// after each part: one launch for its costs, also to the host, and the snapshot of its gates
+// (run-ahead only), and its end event.
 int Group::issue_sweep(int par, const std::vector<int> &active) {
   Issued &is = issued_[par];
   is.starts = active;
   hipStream_t pst[SweepCtx::kParts];
+  if (!p_.graphs || timer_.on || gdirty_ || !gexec_) end_ = SweepEnd{};
+  ctx_.end = &end_;
+  int rc;
   if (ctx_.grouped && !p_.graphs && !timer_.on) {
     is.parts = sweep_parts(ctx_, is.off, is.pn, pst);
-    QFS_TRY(fp64_ ? sweep_grouped<double>(ctx_, true, true) : sweep_grouped<float>(ctx_, true, true));
+    rc = fp64_ ? sweep_grouped<double>(ctx_, true, true) : sweep_grouped<float>(ctx_, true, true);
   } else {
     is.parts = 1;
     is.off[0] = 0;
     is.pn[0] = ctx_.nslots;
     pst[0] = stream_;
-    QFS_TRY(sweep_once());
+    rc = sweep_once();
   }
+  ctx_.end = nullptr;
+  QFS_TRY(rc);
+  end_.costs = costs_.as<double>();
+  end_.starts = S_;
+  end_.snap = spec_ ? snap_copy(par, false) : SlotCopy{};
   for (int p = 0; p < is.parts; ++p) {
-    if (spec_) QFS_TRY(launch_copy_slots(ctx_.slots + is.off[p], is.pn[p], snap_copy(par, false), pst[p]));
-    QFS_HIP(hipMemcpyAsync(cost_buf(par, p), costs_.ptr, sizeof(double) * 3 * S_, hipMemcpyDeviceToHost, pst[p]));
+    end_.host = cost_buf(par, p);
+    QFS_TRY(launch_sweep_end(ctx_.slots + is.off[p], is.pn[p], end_, pst[p]));
     QFS_HIP(hipEventRecord(done_[par][p], pst[p]));
   }
   return QFS_OK;

@@ -581,8 +581,7 @@ int launch_narrow(int64_t count, const c128 *src, c64 *dst, hipStream_t s) {
   return QFS_OK;
 }
 
-__global__ void k_copy_slots(const int32_t *slots, SlotCopy c) {
-  const int64_t s = slots[blockIdx.y];
+__device__ __forceinline__ void copy_slot(const SlotCopy &c, int64_t s) {
   for (int b = 0; b < SlotCopy::kBufs; ++b) {
     const int64_t u = c.units[b];
     if (u == 0) continue;
@@ -593,12 +592,46 @@ __global__ void k_copy_slots(const int32_t *slots, SlotCopy c) {
   }
 }
 
-int launch_copy_slots(const int32_t *slots, int nslots, const SlotCopy &c, hipStream_t s) {
-  if (nslots <= 0) return QFS_OK;
+__global__ void k_copy_slots(const int32_t *slots, SlotCopy c) { copy_slot(c, slots[blockIdx.y]); }
+
+// Bound by its launch: in the place of a launch per cost, one for the snapshot and a copy to
+// the host, of which each took 2 to 4 us with as much again between them (3 qubits), and 20 to
+// 28 us beside the other part's passes (12 qubits, M = 256, 16 starts).
+__global__ __launch_bounds__(256) void k_sweep_end(const int32_t *slots, SweepEnd e) {
+  const int s = slots[blockIdx.y], i = threadIdx.x >> 6;
+  if (blockIdx.x == 0 && i < 2 && e.n[i] > 0) {
+    double sum = 0.0;
+    for (int b = threadIdx.x & 63; b < e.n[i]; b += 64) sum += e.part[i][(int64_t)s * e.stride[i] + b];
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) sum += __shfl_down(sum, o);
+    if ((threadIdx.x & 63) == 0) {
+      sum *= 1.0 / e.m[i];
+      e.costs[i * e.starts + s] = sum;
+      e.host[i * e.starts + s] = sum;
+      __threadfence_system();
+    }
+  }
+  copy_slot(e.snap, s);
+}
+
+// Blocks of 256 threads a start for the copies of c.
+unsigned copy_blocks(const SlotCopy &c) {
   int64_t umax = 0;
   for (int b = 0; b < SlotCopy::kBufs; ++b) umax = std::max(umax, c.units[b]);
-  if (umax == 0) return QFS_OK;
-  const unsigned bx = (unsigned)std::min<int64_t>((umax + 255) / 256, 64);
+  return (unsigned)std::min<int64_t>((umax + 255) / 256, 64);
+}
+
+int launch_sweep_end(const int32_t *slots, int nslots, const SweepEnd &e, hipStream_t s) {
+  if (nslots <= 0) return QFS_OK;
+  hipLaunchKernelGGL(k_sweep_end, dim3(std::max(1u, copy_blocks(e.snap)), (unsigned)nslots), dim3(256), 0, s, slots,
+                     e);
+  QFS_HIP(hipGetLastError());
+  return QFS_OK;
+}
+
+int launch_copy_slots(const int32_t *slots, int nslots, const SlotCopy &c, hipStream_t s) {
+  const unsigned bx = copy_blocks(c);
+  if (nslots <= 0 || bx == 0) return QFS_OK;
   hipLaunchKernelGGL(k_copy_slots, dim3(bx, (unsigned)nslots), dim3(256), 0, s, slots, c);
   QFS_HIP(hipGetLastError());
   return QFS_OK;

@@ -257,6 +257,19 @@ struct SlotCopy {
   int64_t units[kBufs] = {};
 };
 int launch_copy_slots(const int32_t *slots, int nslots, const SlotCopy &c, hipStream_t s);
+// What ends a sweep of the starts slots[0 .. nslots): their costs (entry 0: training, 1:
+// validation; n[i] = 0: none) as the fixed-order sum of part[i][start * stride[i] + 0 .. n[i])
+// over m[i], to costs[i * starts + start] and, in pinned host memory, host[the same]; and the
+// copies of snap (units 0: none).
+struct SweepEnd {
+  const double *part[2] = {};
+  int n[2] = {}, stride[2] = {};
+  double m[2] = {};
+  double *costs = nullptr, *host = nullptr;
+  int starts = 0;
+  SlotCopy snap;
+};
+int launch_sweep_end(const int32_t *slots, int nslots, const SweepEnd &e, hipStream_t s);
 int launch_zero(void *p, size_t bytes, hipStream_t s);
 // A[i][i] = 1 for i < N in an N x ld complex128 matrix (the computational basis as columns).
 int launch_unit_columns(int64_t N, int64_t ld, c128 *A, hipStream_t s);
