@@ -2,7 +2,9 @@
 // Gram-Schmidt projection) and the dense-target product, plus layout conversions.
 #include <algorithm>
 
+#include "polar4.h"
 #include "qfs_internal.h"
+#include "stream_common.h"
 
 namespace qfs {
 
@@ -246,87 +248,123 @@ static int gram_splitk(int m, int n, int k, const c128 *A, int lda, const c128 *
 }
 
 // ------------------------------------------------------------------ Cholesky, R^-1
-// In-place upper Cholesky G = R^H R of an m x m Hermitian positive-definite matrix
-// (row-major, ld m), right-looking: R[j][j] = sqrt(G[j][j]), R[j][c] = G[j][c] / R[j][j],
-// G[i][c] -= conj(R[j][i]) R[j][c] for i, c > j. flag[0] is set on a non-positive pivot.
-// Blocked: rows [j, j + b) of the trailing matrix (the
-// "row panel", b x w with w = m - j, in LDS) are factored by one work-group with the
-// column steps above restricted to the panel; the rest of the trailing matrix is then
-// updated with one GEMM, G[j+b:, j+b:] -= R[J, j+b:]^H R[J, j+b:]. Only the upper
-// triangle is ever read; the strictly lower part is cleared at the end.
-__global__ __launch_bounds__(1024) void k_chol_panel(int m, int j, int b, c128 *G, int *flag) {
-  extern __shared__ c128 pan[];  // [b][w]
-  __shared__ double inv_pivot;
-  const int tid = threadIdx.x, nt = blockDim.x, w = m - j;
-  for (int e = tid; e < b * w; e += nt) {
-    const int r = e / w, c = e % w;
-    pan[e] = G[(int64_t)(j + r) * m + j + c];
+// Upper Cholesky G = R^H R of an m x m Hermitian positive-definite matrix (row-major, ld m) in
+// place, right-looking in panels of kCholB rows. flag[0] is set on a non-positive pivot. Only
+// the upper triangle and the real parts of the diagonal are read.
+//
+// One launch per panel, the 64 columns of a work-group solved beside the other groups'. Every
+// work-group factors the diagonal block for itself, in 32 steps of one barrier each: thread
+// (c, g) holds rows g, g + 8, g + 16, g + 24 of column c; the owners of row j put it into LDS as
+// it is, and all threads subtract conj(row j) row j / pivot from the rows they hold (rows up to j
+// get values that nobody reads). Then R_JJ^H X = G_J by columns: four lanes per column with every
+// fourth row each, a finished row going round the four by a quad exchange.
+// The diagonal block stays as it is for the other work-groups; its factor goes, transposed and
+// conjugated, below the diagonal, the pivots' roots into the diagonal's imaginary parts, and
+// k_chol_finish puts both in place.
+// Bound by the chain of steps: 16 us a panel of a 256 x 256 matrix and 10.6 of a 32 x 32 one,
+// where one work-group with the panel in LDS and three barriers a step took 45 and 22.
+constexpr int kCholB = 32;
+
+__global__ __launch_bounds__(256) void k_chol_panel(int m, int j, int b, c128 *G, int *flag) {
+  __shared__ c128 R[kCholB][kCholB + 1];
+  __shared__ double inv[kCholB];
+  const int tid = threadIdx.x;
+  const int64_t ld = m;
+  const int q = tid & 3, col = j + b + blockIdx.x * 64 + (tid >> 2);
+  c128 y[kCholB / 4];
+#pragma unroll
+  for (int i = 0; i < kCholB / 4; ++i) {
+    const int r = 4 * i + q;
+    y[i] = r < b && col < m ? G[(j + r) * ld + col] : cmake(0.0, 0.0);
   }
-  __syncthreads();
-  for (int jj = 0; jj < b; ++jj) {
+  const int c = tid & 31, g = tid >> 5;
+  c128 v[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int r = g + 8 * k;
+    v[k] = r <= c && c < b ? G[(j + r) * ld + j + c] : cmake(r == c ? 1.0 : 0.0, 0.0);
+  }
+#pragma unroll
+  for (int jj = 0; jj < kCholB; ++jj) {
+    if (g == (jj & 7)) R[jj][c] = v[jj >> 3];
+    lds_barrier();
+    const double d = R[jj][jj].re;
+    const bool ok = d > 0.0;
+    const double ip = ok ? rsq_nr(d) : 0.0;
     if (tid == 0) {
-      const double d = pan[jj * w + jj].re;
-      if (!(d > 0.0)) {
-        flag[0] = 1;
-        inv_pivot = 0.0;
-        pan[jj * w + jj] = cmake(1.0, 0.0);
-      } else {
-        const double r = sqrt(d);
-        pan[jj * w + jj] = cmake(r, 0.0);
-        inv_pivot = 1.0 / r;
-      }
+      inv[jj] = ip;
+      if (!ok && blockIdx.x == 0) flag[0] = 1;
     }
-    __syncthreads();
-    const double ip = inv_pivot;
-    for (int c = jj + 1 + tid; c < w; c += nt) pan[jj * w + c] = cscale(pan[jj * w + c], ip);
-    __syncthreads();
-    // rows jj+1 .. b-1 of the panel, columns from the row's diagonal on
-    const int rows = b - jj - 1;
-    for (int e = tid; e < rows * w; e += nt) {
-      const int ii = jj + 1 + e / w, c = e % w;
-      if (c < ii) continue;
-      c128 v = pan[ii * w + c];
-      cfma(v, cscale(cconj(pan[jj * w + ii]), -1.0), pan[jj * w + c]);
-      pan[ii * w + c] = v;
-    }
-    __syncthreads();
+    const c128 x = cscale(R[jj][c], -ip * ip);
+#pragma unroll
+    for (int k = jj >> 3; k < 4; ++k) cfma_conj(v[k], x, R[jj][g + 8 * k]);
   }
-  for (int e = tid; e < b * w; e += nt) {
-    const int r = e / w, c = e % w;
-    G[(int64_t)(j + r) * m + j + c] = pan[e];
+  lds_barrier();
+  // R_JJ above the diagonal, zero elsewhere; the pivots' roots
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int r = g + 8 * k;
+    const c128 x = R[r][c];
+    const double ip = inv[r];
+    R[r][c] = r < c ? cscale(x, ip) : cmake(0.0, 0.0);
+    if (blockIdx.x == 0 && c < b) {
+      if (r < c) G[(j + c) * ld + j + r] = cconj(cscale(x, ip));
+      if (r == c) G[(j + r) * ld + j + r].im = ip > 0.0 ? x.re * ip : 1.0;
+    }
+  }
+  lds_barrier();
+  if (col - (tid >> 2) >= m) return;
+#define QFS_CHOL_ROW(K)                                                            \
+  {                                                                                \
+    const int jj = 4 * i + K;                                                      \
+    const double ip = inv[jj];                                                     \
+    const c128 x = cmake(dpp_move<0x55 * K>(y[i].re * ip), dpp_move<0x55 * K>(y[i].im * ip)); \
+    if (q == K) y[i] = x;                                                          \
+    const c128 nx = cmake(-x.re, -x.im);                                           \
+    _Pragma("unroll") for (int k = i; k < kCholB / 4; ++k) cfma_conj(y[k], nx, R[jj][4 * k + q]); \
+  }
+#pragma unroll
+  for (int i = 0; i < kCholB / 4; ++i) {
+    QFS_CHOL_ROW(0) QFS_CHOL_ROW(1) QFS_CHOL_ROW(2) QFS_CHOL_ROW(3)
+  }
+#undef QFS_CHOL_ROW
+#pragma unroll
+  for (int i = 0; i < kCholB / 4; ++i) {
+    const int r = 4 * i + q;
+    if (r < b && col < m) G[(j + r) * ld + col] = y[i];
   }
 }
 
-__global__ void k_zero_lower(int m, c128 *G) {
+// The diagonal blocks' factors into place, zero below the diagonal.
+__global__ void k_chol_finish(int m, c128 *G) {
   const int64_t total = (int64_t)m * m;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
        e += (int64_t)gridDim.x * blockDim.x) {
     const int i = (int)(e / m), c = (int)(e % m);
-    if (c < i) G[e] = cmake(0.0, 0.0);
+    if (c > i) continue;
+    const c128 x = G[e];
+    if (c == i) {
+      G[e] = cmake(x.im, 0.0);
+    } else {
+      if (i / kCholB == c / kCholB) G[(int64_t)c * m + i] = cconj(x);
+      G[e] = cmake(0.0, 0.0);
+    }
   }
 }
 
 static int cholesky_upper_blocked(int m, c128 *G, int *flag, hipStream_t s) {
-  constexpr size_t kPanelLds = 144 * 1024;
-  static size_t attr = 0;
-  QFS_TRY(ensure_dynamic_lds(reinterpret_cast<const void *>(&k_chol_panel), kPanelLds, &attr));
   const c128 one = cmake(1.0, 0.0), mone = cmake(-1.0, 0.0);
-  for (int j = 0; j < m;) {
-    const int w = m - j;
-    int b = (int)std::min<size_t>(32, kPanelLds / ((size_t)w * sizeof(c128)));
-    b = std::max(1, std::min(b, w));
-    hipLaunchKernelGGL(k_chol_panel, dim3(1), dim3(1024), sizeof(c128) * (size_t)b * w, s, m, j, b, G,
-                       flag);
+  for (int j = 0; j < m; j += kCholB) {
+    const int b = std::min(kCholB, m - j), rest = m - j - b;
+    hipLaunchKernelGGL(k_chol_panel, dim3((unsigned)std::max(1, (rest + 63) / 64)), dim3(256), 0, s, m, j, b, G, flag);
     QFS_HIP(hipGetLastError());
-    const int rest = w - b;
     if (rest > 0) {
       const c128 *panel = G + (int64_t)j * m + j + b;
       QFS_TRY(launch_zgemm(true, rest, rest, b, mone, panel, m, panel, m, one,
                            G + (int64_t)(j + b) * m + j + b, m, s));
     }
-    j += b;
   }
-  hipLaunchKernelGGL(k_zero_lower, dim3((unsigned)std::min<int64_t>(((int64_t)m * m + 255) / 256, 4096)),
+  hipLaunchKernelGGL(k_chol_finish, dim3((unsigned)std::min<int64_t>(((int64_t)m * m + 255) / 256, 4096)),
                      dim3(256), 0, s, m, G);
   QFS_HIP(hipGetLastError());
   return QFS_OK;
