@@ -412,9 +412,13 @@ __device__ __forceinline__ void run_job(const BatchArgs &A, int jid, Pk<R> *buf,
 }
 
 // SCR: the sets in this work-group's global slot instead of LDS (an instantiation of its own, so
-// that either kind is accessed by its own instructions).
+// that either kind is accessed by its own instructions). Three waves a SIMD, at the price of a few
+// registers kept in scratch around the polar factor: with the 190 it would take, eight waves fill
+// a compute unit, and the classes of other sizes wait for the one with the largest sets (128
+// problems of 5-7 qubits: 2.63 -> 2.50 ms the longest class, 0.95 -> 0.84 the next; four waves a
+// SIMD spill more and gain nothing further).
 template <typename R, int NT, bool SCR>
-__global__ __launch_bounds__(NT) void k_batch_sweep(BatchArgs A) {
+__global__ __launch_bounds__(NT, 3) void k_batch_sweep(BatchArgs A) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   __shared__ SweepShared<NT / 64> sh;
   __shared__ int qi_s;
