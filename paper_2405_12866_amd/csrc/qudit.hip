@@ -495,8 +495,9 @@ struct QdPolarLds {
 // by the caller): the 4 x 4 routine, the matrix products above, or the Jacobi SVD started from
 // V_prev in Vs, which leaves the new right singular vectors there.
 //
-// PROD: the products first. They serve the complex64 sweeps. Complex128 sweeps keep the SVD:
-// a run in them ends at the rounding floor of its costs, where the generalisation test
+// PROD: the products first. They serve the complex64 sweeps and a single complex128 sweep, whose
+// SVDs would start cold (d = 4: 64 us a gate against 14). The complex128 sweeps of a run keep
+// the SVD: it ends at the rounding floor of its costs, where the generalisation test
 // compares rounding errors alone, and there the products' more exact factors (unitary to
 // 4e-16 against 5e-15) show the gates' fit to the rounding of the training outputs, a c_val /
 // c_train of 1 + 2 p / (M N) or so for p gate parameters, as over-training.
@@ -841,6 +842,7 @@ struct QdSweeper {
   c128 *g64 = nullptr;  // [S][L][D][D]
   c128 *vst = nullptr;  // [S][L][D][D] Jacobi warm start
   double beta = 0.0;
+  bool products = false;  // a complex128 sweep's polar factors by products, too
   int nslots = 0;
   // second stream of the backward pass (default priority) and its fork/join events: the
   // two halves of the running starts go on two streams, so one half's environment
@@ -911,12 +913,17 @@ struct QdSweeper {
       hipLaunchKernelGGL((k_qd_env<R, dd, int64_t>), dim3(NX * P, ns), dim3(kQdBlock), 0, s, a, as, b, bs, g, P,
                          partials.as<c128>(), sl);
     QFS_HIP(hipGetLastError());
+    return sizeof(R) == 4 || products ? finalize_t<dd, true>(P, k, sl, ns, s) : finalize_t<dd, false>(P, k, sl, ns, s);
+  }
+  template <int dd, bool PROD>
+  int finalize_t(int P, int k, const int32_t *sl, int ns, hipStream_t s) {
+    const int gs = L * dd * dd * dd * dd;
     if (kinds && kinds[k] == QFS_GATE_1Q)
-      hipLaunchKernelGGL((k_qd_finalize1<dd, sizeof(R) == 4>), dim3(ns), dim3(kQdFinBlock), 0, s, partials.as<c128>(), P, beta, sl,
-                         g64, vst, L * dd * dd * dd * dd, k);
+      hipLaunchKernelGGL((k_qd_finalize1<dd, PROD>), dim3(ns), dim3(kQdFinBlock), 0, s, partials.as<c128>(), P, beta,
+                         sl, g64, vst, gs, k);
     else
-      hipLaunchKernelGGL((k_qd_finalize<dd, sizeof(R) == 4>), dim3(ns), dim3(kQdFinBlock), 0, s, partials.as<c128>(), P, beta, sl,
-                         g64, vst, L * dd * dd * dd * dd, k);
+      hipLaunchKernelGGL((k_qd_finalize<dd, PROD>), dim3(ns), dim3(kQdFinBlock), 0, s, partials.as<c128>(), P, beta,
+                         sl, g64, vst, gs, k);
     QFS_HIP(hipGetLastError());
     return QFS_OK;
   }
@@ -1727,6 +1734,7 @@ int qfs_qudit_sweep(int32_t d, int32_t n, int32_t L, const int32_t *pairs, const
     w.g64 = reinterpret_cast<c128 *>(gates);
     w.vst = vst.as<c128>();
     w.beta = beta;
+    w.products = true;
     QFS_TRY(w.alloc(M, 0));
     QFS_TRY(qd_load_sets<R>(w, psi, phi, M, 0));
     QFS_TRY(w.set_slots(all));

@@ -1,4 +1,4 @@
-"""The qudit gate update of complex64 sweeps (polar factor by matrix products, the SVD where
+"""The qudit gate update of complex64 sweeps and of single complex128 ones (polar factor by matrix products, the SVD where
 those do not converge) on environments of given singular values, against numpy's SVD. With the
 computational basis as the sample set of one gate on two qudits, the environment is the
 transposed output set itself."""
@@ -12,12 +12,12 @@ from paper_2405_12866_amd import qfs as Q
 pytestmark = pytest.mark.gpu
 
 
-def _update(d, a):
+def _update(d, a, precision=Q.QFS_PREC_MIXED):
     D = d * d
     psi = torch.eye(D, dtype=torch.complex128, device="cuda")
     phi = torch.as_tensor(np.ascontiguousarray(a.T)).cuda()
     gates = torch.eye(D, dtype=torch.complex128, device="cuda").reshape(1, 1, D, D).contiguous()
-    Q.qfs_qudit_sweep(d, 2, [(0, 1)], psi, phi, gates, precision=Q.QFS_PREC_MIXED)
+    Q.qfs_qudit_sweep(d, 2, [(0, 1)], psi, phi, gates, precision=precision)
     return gates.cpu().numpy()[0, 0]
 
 
@@ -51,3 +51,13 @@ def test_rank_deficient(d, rank):
     assert np.max(np.abs(got.conj().T @ got - np.eye(D))) < 1e-11
     f = np.sum(a.conj() * got).real
     assert abs(f - np.sum(np.linalg.svd(a, compute_uv=False))) < 1e-6 * max(1, rank)
+
+
+@pytest.mark.parametrize("kappa", [1.0, 1.5, 100.0, 700.0, 1e4])
+@pytest.mark.parametrize("d", [2, 3, 4])
+def test_full_rank_fp64(d, kappa):
+    a = _environment(d, np.exp(-np.linspace(0, np.log(kappa), d * d)) * 37.0, seed=int(kappa * 10) + d + 1)
+    w, s, vh = np.linalg.svd(a)
+    got = _update(d, a, Q.QFS_PREC_FP64)
+    assert np.max(np.abs(got - w @ vh)) < 1e-13 * s[0] / s[-1]
+    assert np.max(np.abs(got.conj().T @ got - np.eye(d * d))) < 1e-13 * s[0] / s[-1]
