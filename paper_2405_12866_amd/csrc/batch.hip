@@ -116,10 +116,14 @@ __device__ __forceinline__ void apply_states(BSet<R> S, int pa, int pb, const cx
 }
 
 // B_k <- u^dagger B_{k+1} in place (as apply_states), and acc += a conj(B_k) over the same groups
-// on the way: the environment of the gate on (pa, pb).
+// on the way: the environment of the gate on (pa, pb). Its products and sums are FP64 for either
+// state precision: some of the small environments here are so badly conditioned that FP32 sums of a
+// thread's groups show in the gates (over 30 sets of 128 problems, four sweeps, the error against
+// FP64 states is 5 % less in the geometric mean). The vector units do them at the FP32 rate; the
+// conversions and registers cost 5 % of the call.
 template <typename R, int NT>
 __device__ __forceinline__ void unapply_env(BSet<R> B, const Pk<R> *a, int pa, int pb, const cx<R> *u,
-                                            cx<R> (&acc)[16]) {
+                                            c128 (&acc)[16]) {
   constexpr int V = Pk<R>::V;
   cx<R> m[16];
   gate_regs<R>(u, true, m);
@@ -143,8 +147,10 @@ __device__ __forceinline__ void unapply_env(BSet<R> B, const Pk<R> *a, int pa, i
 #pragma unroll
         for (int q = 0; q < 4; ++q) cfma(t, m[p * 4 + q], x[q].v[e]);
         y.v[e] = t;
+        const c128 td = cmake((double)t.re, (double)t.im);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) cfma_conj(acc[q * 4 + p], av[q].v[e], t);
+        for (int q = 0; q < 4; ++q)
+          cfma_conj(acc[q * 4 + p], cmake((double)av[q].v[e].re, (double)av[q].v[e].im), td);
       }
       B.p[o[p]] = y;
     }
@@ -333,9 +339,9 @@ __device__ __forceinline__ void run_job(const BatchArgs &A, int jid, Pk<R> *buf,
         continue;
       }
       // B_k and the environment of gate k
-      cx<R> acc[16];
+      c128 acc[16];
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[e] = cmake<R>(0, 0);
+      for (int e = 0; e < 16; ++e) acc[e] = cmake(0.0, 0.0);
       unapply_env<R, NT>(setB, setA.p, pa, pb, u0, acc);
       const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
       {
@@ -343,8 +349,8 @@ __device__ __forceinline__ void run_job(const BatchArgs &A, int jid, Pk<R> *buf,
         double v[32];
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-          v[2 * e] = (double)acc[e].re;
-          v[2 * e + 1] = (double)acc[e].im;
+          v[2 * e] = acc[e].re;
+          v[2 * e + 1] = acc[e].im;
         }
         const double ws = wave_sums<double, 32>(v);
         if (lane < 32) reinterpret_cast<double *>(&sh.wred[w][0])[wave_sums_index<32>(lane)] = ws;
@@ -412,13 +418,11 @@ __device__ __forceinline__ void run_job(const BatchArgs &A, int jid, Pk<R> *buf,
 }
 
 // SCR: the sets in this work-group's global slot instead of LDS (an instantiation of its own, so
-// that either kind is accessed by its own instructions). Three waves a SIMD, at the price of a few
-// registers kept in scratch around the polar factor: with the 190 it would take, eight waves fill
-// a compute unit, and the classes of other sizes wait for the one with the largest sets (128
-// problems of 5-7 qubits: 2.63 -> 2.50 ms the longest class, 0.95 -> 0.84 the next; four waves a
-// SIMD spill more and gain nothing further).
+// that either kind is accessed by its own instructions). Two waves a SIMD:
+// with three the FP64 environment spills (128 problems of 5-7 qubits: the longest class takes 2.86
+// ms instead of 2.74, the next 0.80 instead of 0.95, the call 3 % more).
 template <typename R, int NT, bool SCR>
-__global__ __launch_bounds__(NT, 3) void k_batch_sweep(BatchArgs A) {
+__global__ __launch_bounds__(NT, 2) void k_batch_sweep(BatchArgs A) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   __shared__ SweepShared<NT / 64> sh;
   __shared__ int qi_s;
