@@ -473,8 +473,9 @@ struct SweepCtx {
   c128 *partials = nullptr;  // [S][kPcap][16]
   double *dpart0 = nullptr, *dpart1 = nullptr;  // [S][kPcap] each
   double *costs = nullptr;   // [3 S]: c_train, c_val, c_0
-  // set: the sweep leaves its costs' block sums to the launch that ends it, and notes here how
-  // many there are of each start
+  // set: the sweep leaves its costs' block sums to the launches that end its parts, and notes
+  // here, per part, how many there are of each start (a part's launches have block counts of
+  // their own)
   SweepEnd *end = nullptr;
   int S = 0;
   KernelTimer *timer = nullptr;
@@ -622,9 +623,10 @@ int sweep_forward(SweepCtx &c, bool with_c0) {
 // second-moment matrix against the B entry before the group, then the finalize updates the
 // group's gates in order. Item ng: the Eq. 9 cost of the updated gates from
 // a_0 = C^dagger U psi (the last group's operator applied on the way). Item ng + 1: the
-// forward pass of the updated gates and their validation cost.
+// forward pass of the updated gates and their validation cost. The starts are the sweep's
+// part `part`.
 template <typename R>
-int grouped_item(SweepCtx &c, const int32_t *slots, int n, hipStream_t st, int item) {
+int grouped_item(SweepCtx &c, int part, const int32_t *slots, int n, hipStream_t st, int item) {
   cx<R> *psi = static_cast<cx<R> *>(c.psi), *phi = static_cast<cx<R> *>(c.phi);
   cx<R> *B = static_cast<cx<R> *>(c.blist), *A = static_cast<cx<R> *>(c.astate);
   const int64_t sN = c.g.elems();
@@ -633,6 +635,11 @@ int grouped_item(SweepCtx &c, const int32_t *slots, int n, hipStream_t st, int i
   const std::vector<GateGroup> &G = *c.groups;
   const int ng = (int)G.size();
   const double set = set_bytes<R>(c, c.g) * n / c.nslots;
+  SweepCtx sub = c;  // the part alone
+  sub.slots = slots;
+  sub.nslots = n;
+  sub.stream = st;
+  sub.end = c.end ? c.end + part : nullptr;
   LaunchEvents le;
   if (item < ng) {
     const GateGroup &cur = G[item];
@@ -665,12 +672,8 @@ int grouped_item(SweepCtx &c, const int32_t *slots, int n, hipStream_t st, int i
                                  SBuf<R>{psi, 0}, slots, n, group_blocks_per_start(c.nslots), nullptr, kGPcap,
                                  c.dpart0, &P, st, le));
     QFS_TRY(T.ext_end(kClsDist, 2.0 * set));
-    return dist_end(c, 0, P, kGPcap, slots, n, st);
+    return dist_end(sub, 0, P, kGPcap, slots, n, st);
   }
-  SweepCtx sub = c;
-  sub.slots = slots;
-  sub.nslots = n;
-  sub.stream = st;
   return sweep_forward<R>(sub, false);
 }
 
@@ -708,7 +711,7 @@ int sweep_grouped(SweepCtx &c, bool with_forward, bool ordered = false) {
   hipStream_t pst[SweepCtx::kParts];
   const int parts = sweep_parts(c, off, pn, pst);
   if (parts <= 1) {
-    for (int i = 0; i < items; ++i) QFS_TRY(grouped_item<R>(c, c.slots, c.nslots, c.stream, i));
+    for (int i = 0; i < items; ++i) QFS_TRY(grouped_item<R>(c, 0, c.slots, c.nslots, c.stream, i));
     return QFS_OK;
   }
   static const int lag_env = [] {
@@ -723,7 +726,7 @@ int sweep_grouped(SweepCtx &c, bool with_forward, bool ordered = false) {
   for (int t = 0; t < items + lag * (parts - 1); ++t)
     for (int p = 0; p < parts; ++p) {
       const int i = t - p * lag;
-      if (i >= 0 && i < items) QFS_TRY(grouped_item<R>(c, c.slots + off[p], pn[p], pst[p], i));
+      if (i >= 0 && i < items) QFS_TRY(grouped_item<R>(c, p, c.slots + off[p], pn[p], pst[p], i));
     }
   if (!ordered)
     for (int p = 1; p < parts; ++p) {
@@ -926,7 +929,8 @@ class Group {
   // sweep parity and part, written on the part's stream right after its sweep
   double *h_costs_ = nullptr;
   size_t h_costs_bytes_ = 0;
-  SweepEnd end_;  // of the last sweep issued (a graph's counts hold for its replays)
+  // of the last sweep issued, per part (a graph's counts hold for its replays)
+  SweepEnd end_[SweepCtx::kParts];
   double *cost_buf(int par, int part) { return h_costs_ + (size_t)(1 + par * SweepCtx::kParts + part) * 3 * S_; }
   // The control loop's sweeps: run-ahead (spec_), per sweep parity the starts and parts it
   // was issued with and an event per part at its end (timing reference seg0_), and the
@@ -1231,32 +1235,36 @@ int Group::end_segment() {
 // One sweep of the running starts (parity par). A grouped sweep without timing or graphs
 // runs its parts on their streams with no join, each part going on into its next sweep;
 // after each part: one launch for its costs, also to the host, and the snapshot of its gates
-// (run-ahead only), and its end event.
+// (run-ahead only), and its end event. A graph joins the parts, and their ends follow it on
+// the call's stream.
 int Group::issue_sweep(int par, const std::vector<int> &active) {
   Issued &is = issued_[par];
   is.starts = active;
   hipStream_t pst[SweepCtx::kParts];
-  if (!p_.graphs || timer_.on || gdirty_ || !gexec_) end_ = SweepEnd{};
-  ctx_.end = &end_;
+  if (!p_.graphs || timer_.on || gdirty_ || !gexec_)
+    for (SweepEnd &e : end_) e = SweepEnd{};
+  ctx_.end = end_;
+  is.parts = 1;
+  is.off[0] = 0;
+  is.pn[0] = ctx_.nslots;
+  pst[0] = stream_;
+  if (ctx_.grouped) is.parts = sweep_parts(ctx_, is.off, is.pn, pst);
   int rc;
   if (ctx_.grouped && !p_.graphs && !timer_.on) {
-    is.parts = sweep_parts(ctx_, is.off, is.pn, pst);
     rc = fp64_ ? sweep_grouped<double>(ctx_, true, true) : sweep_grouped<float>(ctx_, true, true);
   } else {
-    is.parts = 1;
-    is.off[0] = 0;
-    is.pn[0] = ctx_.nslots;
-    pst[0] = stream_;
+    for (hipStream_t &s : pst) s = stream_;
     rc = sweep_once();
   }
   ctx_.end = nullptr;
   QFS_TRY(rc);
-  end_.costs = costs_.as<double>();
-  end_.starts = S_;
-  end_.snap = spec_ ? snap_copy(par, false) : SlotCopy{};
   for (int p = 0; p < is.parts; ++p) {
-    end_.host = cost_buf(par, p);
-    QFS_TRY(launch_sweep_end(ctx_.slots + is.off[p], is.pn[p], end_, pst[p]));
+    SweepEnd &e = end_[p];
+    e.costs = costs_.as<double>();
+    e.starts = S_;
+    e.snap = spec_ ? snap_copy(par, false) : SlotCopy{};
+    e.host = cost_buf(par, p);
+    QFS_TRY(launch_sweep_end(ctx_.slots + is.off[p], is.pn[p], e, pst[p]));
     QFS_HIP(hipEventRecord(done_[par][p], pst[p]));
   }
   return QFS_OK;
