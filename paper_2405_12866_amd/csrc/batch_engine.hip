@@ -486,7 +486,12 @@ int qfs::batch_instantiate(int32_t P, const qfs_template *tmpl, const qfs_target
     if (!plan.empty()) {
       const int nl = (int)plan.size();
       if ((size_t)nl * 16 * sizeof(int32_t) > dhead.bytes) QFS_TRY(dhead.alloc((size_t)nl * 16 * sizeof(int32_t)));
-      if (sfill > scratch.bytes) QFS_TRY(scratch.alloc(sfill));
+      if (sfill > scratch.bytes) {
+        // (every launch of the rounds before has been waited for)
+        scratch.release();
+        BufferScope::recycle(p.device_mem_budget ? 0 : BufferScope::kKeepSmall);
+        QFS_TRY(scratch.alloc(sfill));
+      }
       QFS_HIP(hipMemcpyAsync(dqueue.ptr, qhost.data(), sizeof(int32_t) * qfill, hipMemcpyHostToDevice, st));
       QFS_TRY(launch_zero(dhead.ptr, (size_t)nl * 16 * sizeof(int32_t), st));
       QFS_HIP(hipEventRecord(e0, st));

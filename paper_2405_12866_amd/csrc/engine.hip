@@ -175,6 +175,19 @@ int BufferScope::done(hipStream_t s) {
 void BufferScope::give_back(void *self, void *p, size_t bytes) {
   static_cast<BufferScope *>(self)->kept_.emplace_back(p, bytes);
 }
+void BufferScope::recycle(size_t keep) {
+  BufferScope *sc = t_scope;
+  if (!sc) return;
+  std::vector<std::pair<void *, size_t>> small;
+  for (auto &b : sc->kept_) {
+    if (b.second > keep)
+      (void)hipFree(b.first);
+    else
+      small.push_back(b);
+  }
+  sc->kept_.clear();
+  device_cache_put(sc->dev_, small);
+}
 int BufferScope::alloc(DevBuf &b, size_t bytes) {
   // size classes, so that calls of like sizes find each other's blocks: powers of two up to
   // 1 MiB, eighths of one beyond (at most an eighth more than asked for)

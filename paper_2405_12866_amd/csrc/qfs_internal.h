@@ -121,7 +121,8 @@ struct DevBuf;
 // and the blocks released go back to it when the scope ends. hipMalloc and hipFree of the
 // working sets cost far more than the kernels of a step entry (an 11-qubit FP64 sweep of 5
 // starts: 14.8 ms a call with them, 0.69 without). A block released inside a call is not handed
-// out again before its end, so kernels still queued on any of the call's streams keep it.
+// out again before its end, so kernels still queued on any of the call's streams keep it,
+// unless the call knows that the work that used it has ended and says so by recycle().
 // done(): waits for the call's stream, after which its blocks are idle; a scope that ends
 // without it (an error path) waits for the whole device.
 class BufferScope {
@@ -133,6 +134,12 @@ class BufferScope {
   int done(hipStream_t s);
   int alloc(DevBuf &b, size_t bytes);
   static BufferScope *current();
+  // For a call that has waited for all its work and goes on with buffers of other sizes: of the
+  // blocks the open scope has been given, those above `keep` bytes are freed (a call holds its
+  // live buffers, not those of its earlier stages beside them), the others kept for reuse
+  // (kKeepSmall: about 1 GiB of a run's doublings at most, half a percent of the device).
+  static constexpr size_t kKeepSmall = size_t(1) << 26;
+  static void recycle(size_t keep);
 
  private:
   static void give_back(void *self, void *p, size_t bytes);

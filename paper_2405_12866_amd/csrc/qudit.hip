@@ -826,6 +826,10 @@ int64_t qd_pow(int d, int e) {
   return r;
 }
 
+// Blocks of the open BufferScope that a run keeps between its stages (doublings, the switch of
+// precision, groups of starts): none under a memory budget of its own.
+size_t qd_keep(const qfs_params &p) { return p.device_mem_budget ? 0 : BufferScope::kKeepSmall; }
+
 int qd_grid(int64_t items) { return (int)std::min<int64_t>((items + kQdBlock - 1) / kQdBlock, 4096); }
 
 // One problem's device state: the sweep machinery over `S` starts for state precision R.
@@ -942,6 +946,11 @@ struct QdSweeper {
   }
 
   size_t budget = 0;  // device bytes the sweeper may hold (0: as much as allocates)
+
+  // Gives the buffers that follow M back, ahead of an alloc for another M.
+  void release() {
+    for (DevBuf *b : {&psi, &phi, &psiv, &phiv, &blist, &astate, &vstate, &partials, &dpart}) b->release();
+  }
 
   int alloc(int Mnew, int Mvnew) {
     M = Mnew;
@@ -1157,6 +1166,7 @@ struct QdData {
   const qfs_target *tgt = nullptr;  // drawn sets: DENSE or CIRCUIT target
   uint64_t seed = 0;
   int m_val = 0;
+  size_t keep = 0;  // BufferScope::recycle's bound
   int M = 0, Mv = 0, generation = 0;
   bool one_stream = false;  // the sweeps keep to the call's stream
   DevBuf tpsi, tphi, vpsi, vphi, work, slot0;
@@ -1221,6 +1231,8 @@ struct QdData {
     QFS_HIP(hipStreamSynchronize(st));
     tpsi.swap(np);
     tphi.swap(nf);
+    for (DevBuf *b : {&np, &nf, &vpsi, &vphi}) b->release();
+    BufferScope::recycle(keep);
     M = Mnew;
     ++generation;
     return draw_validation(M);
@@ -1290,6 +1302,7 @@ int qd_run(int d, const qfs_template *t, QdData &data, const qfs_params &p, c128
   } guard{e0, e1};
   QFS_TRY(w.forward(cs.need_c0));
   QFS_TRY(read());
+  BufferScope::recycle(data.keep);  // (the set-up's work space)
   if (cs.need_c0) {
     for (int s : active) cs.c_prev[s] = h[2 * S + s];
     cs.need_c0 = false;
@@ -1340,6 +1353,8 @@ int qd_run(int d, const qfs_template *t, QdData &data, const qfs_params &p, c128
           active.push_back(s);
         }
       QFS_HIP(hipStreamSynchronize(w.st));
+      w.release();
+      BufferScope::recycle(data.keep);
       QFS_TRY(data.grow(cs.M));
       n_val = data.val_rows();
       QFS_TRY(w.alloc(cs.M, n_val));
@@ -1348,6 +1363,7 @@ int qd_run(int d, const qfs_template *t, QdData &data, const qfs_params &p, c128
       QFS_TRY(w.set_slots(active));
       QFS_TRY(w.forward(true));
       QFS_TRY(read());
+      BufferScope::recycle(data.keep);
       for (int s : active) cs.c_prev[s] = h[2 * S + s];
       continue;
     }
@@ -1395,6 +1411,7 @@ int qd_group(int d, const qfs_template *tmpl, const QdData &cfg, const qfs_param
   data.tgt = cfg.tgt;
   data.seed = cfg.seed;
   data.m_val = cfg.m_val;
+  data.keep = qd_keep(p);
   data.one_stream = cfg.one_stream;
   data.d = d;
   data.n = n;
@@ -1459,6 +1476,8 @@ int qd_group(int d, const qfs_template *tmpl, const QdData &cfg, const qfs_param
   if (p.precision == QFS_PREC_MIXED) {
     QFS_TRY(qd_run<float>(d, tmpl, data, p, gates.as<c128>(), vstore.as<c128>(), S, cs, t0, refine));
     if (refine) {
+      // (the complex64 run ended with a wait for its last sweep)
+      BufferScope::recycle(data.keep);
       r.refined = 1;
       QFS_TRY(qd_run<double>(d, tmpl, data, p, gates.as<c128>(), vstore.as<c128>(), S, cs, t0, refine));
     }
@@ -1500,13 +1519,15 @@ int qd_split(int d, const qfs_template *tmpl, const QdData &cfg, const qfs_param
   QdGroupResult r;
   const int rc = qd_group(d, tmpl, cfg, p, gates_in, start0, S, t0, r);
   if (rc == QFS_ENOMEM && S > 1) {
-    (void)hipStreamSynchronize(static_cast<hipStream_t>(p.hip_stream));
+    if (hipStreamSynchronize(static_cast<hipStream_t>(p.hip_stream)) == hipSuccess) BufferScope::recycle(qd_keep(p));
     (void)hipGetLastError();
     const int h = S / 2;
     QFS_TRY(qd_split(d, tmpl, cfg, p, gates_in, start0, h, t0, results));
     return qd_split(d, tmpl, cfg, p, gates_in, start0 + h, S - h, t0, results);
   }
   if (rc != QFS_OK) return rc;
+  // (the group has waited for its stream; the next one starts without its buffers)
+  if (S < p.multistarts) BufferScope::recycle(qd_keep(p));
   results.push_back(std::move(r));
   return QFS_OK;
 }
