@@ -190,11 +190,12 @@ void BufferScope::recycle(size_t keep) {
 }
 int BufferScope::alloc(DevBuf &b, size_t bytes) {
   // size classes, so that calls of like sizes find each other's blocks: powers of two up to
-  // 1 MiB, eighths of one beyond (at most an eighth more than asked for)
+  // 1 MiB, eighths of one up to 16 MiB, multiples of 2 MiB beyond (the sets of large calls are
+  // sized against the device or a budget: a class adds 2 MiB to them at most)
   size_t cls = 256;
   while (cls < bytes && cls < (size_t(1) << 20)) cls <<= 1;
   if (cls < bytes) {
-    while (cls * 2 <= bytes) cls <<= 1;
+    while (cls * 2 <= bytes && cls < (size_t(1) << 24)) cls <<= 1;
     cls = (bytes + cls / 8 - 1) / (cls / 8) * (cls / 8);
   }
   void *p = device_cache_take(dev_, cls);

@@ -1,6 +1,6 @@
 """Device memory of calls that go on with buffers of other sizes: a qudit run that doubles its
 training set, or is split into groups of starts by a memory budget, holds its live buffers and
-not those of its earlier stages."""
+not those of its earlier stages; buffers of large calls take up what was asked for."""
 import threading
 
 import numpy as np
@@ -80,3 +80,16 @@ def test_groups_of_starts():
     L, used, info = _run(7, 512, 16, 8, m_init=512, fixed_m=1, max_iter=3, device_mem_budget=budget)
     assert L == 3 and info["start_groups"] == 4
     assert used < 1.25 * budget, (used / MB, budget / MB)
+
+
+def test_block_sizes():
+    """What one sweep's buffers are kept as, against their sizes: 2 % above at most (2 MiB a
+    block and its small buffers; eighths would add 11 % to this one's B lists)."""
+    d, n, M, S, L = 3, 9, 64, 15, 9
+    N = d ** n
+    pairs = [(q % (n - 1), q % (n - 1) + 1) for q in range(L)]
+    psi, phi = _states(N, M, 1), _states(N, M, 2)
+    gates = torch.eye(9, dtype=torch.complex128, device="cuda").repeat(S, L, 1, 1).contiguous()
+    Q.qfs_release_device_cache()
+    Q.qfs_qudit_sweep(d, n, pairs, psi, phi, gates, Q.QFS_PREC_MIXED)
+    assert Q.qfs_release_device_cache() < 1.02 * _live(N, M, 0, L, S)
