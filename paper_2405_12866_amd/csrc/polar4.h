@@ -235,10 +235,11 @@ __device__ __forceinline__ void polar4_wave(const c128 *G, double beta, const c1
       return;
     }
     // the Jacobi forms fourth powers of the entries: scaled by a power of two (exact, and the
-    // polar factor does not change) where those leave the range of a double
+    // polar factor does not change) where those leave the range of a double (a subnormal entry
+    // asks for more than the largest power of two; 2^1000 brings it far enough)
     const c128 x0 = gm(r, c);
     const double big = row16_max(fmax(fabs(x0.re), fabs(x0.im)));
-    if (big > 1e60 || big < 1e-60) scale = big > 0.0 ? ldexp(1.0, -ilogb(big)) : 1.0;
+    if (big > 1e60 || big < 1e-60) scale = big > 0.0 ? ldexp(1.0, min(-ilogb(big), 1000)) : 1.0;
   }
   if (vstore) {
     // lane 4c + r holds X[r][c]; Y[a][c] = sum_k conj(X[k][a]) X[k][c] (quad c);
