@@ -24,10 +24,24 @@ __device__ inline void polar2_update(const c128 *G, double beta, c128 *u64, cx<R
       const c128 g1 = G[(2 * q) * 4 + 2 * p] + G[(2 * q + 1) * 4 + 2 * p + 1];
       x[q * 2 + p] = cscale(g1, 1.0 - beta) + cscale(u64[(2 * q) * 4 + 2 * p], beta);
     }
-  const c128 det = x[0] * x[3] - x[1] * x[2];
+  c128 det;
+  double d2;
+  for (int pass = 0;; ++pass) {
+    det = x[0] * x[3] - x[1] * x[2];
+    d2 = cabs2(det);
+    if (pass || (d2 > 1e-280 && d2 < 1e280)) break;
+    // fourth powers of the entries near the ends of a double's range, or a singular X: once
+    // more with the largest entry near one (by a power of two, which changes no factor)
+    double big = 0.0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) big = fmax(big, fmax(fabs(x[e].re), fabs(x[e].im)));
+    if (!(big > 0.0)) return;
+    const double scale = ldexp(1.0, min(-ilogb(big), 1000));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = cscale(x[e], scale);
+  }
   // 1 / |det| and 1 / norm by rsq_nr: about one ulp, and a short chain (this runs on one thread)
-  const double d2 = cabs2(det);
-  const c128 w = d2 > 0.0 ? cscale(det, rsq_nr(d2)) : cmake(1.0, 0.0);
+  const c128 w = d2 > 1e-300 ? cscale(det, rsq_nr(d2)) : cmake(1.0, 0.0);
   c128 y[4] = {x[0] + w * cconj(x[3]), x[1] - w * cconj(x[2]), x[2] - w * cconj(x[1]),
                x[3] + w * cconj(x[0])};
   const double n2 = ((cabs2(y[0]) + cabs2(y[1])) + (cabs2(y[2]) + cabs2(y[3]))) * 0.5;
