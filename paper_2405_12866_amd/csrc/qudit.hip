@@ -255,10 +255,14 @@ __global__ __launch_bounds__(kQdBlock) void k_qd_env(const cx<R> *a, int64_t a_s
 // small changes converges in a few Jacobi sweeps; the new V is stored back.
 // u for a (near) singular environment: left vectors in decreasing-sigma order,
 // orthonormalised in place in LDS (W column kk in Tm[. * D + kk]) and completed with unit
-// vectors (any such completion attains the maximum); one thread.
-template <int D, int PL>
-__device__ __noinline__ void qd_polar_singular(const c128 (*Gc)[16], const c128 (*Vc)[16], c128 *Tm,
-                                               const double *sig, double smax, c128 *u) {
+// vectors (any such completion attains the maximum); one thread. A function per workspace: with
+// one caller its LDS addresses are constants, and its serial chain of LDS accesses, hundreds of
+// microseconds for D = 9 and milliseconds for D = 16, is a quarter longer without.
+template <typename WS, int D>
+__device__ __noinline__ void qd_polar_singular(WS &W, double smax) {
+  const auto &Gc = W.Gc, &Vc = W.Vc;
+  c128 *Tm = W.Tm, *u = W.Pu;
+  const double *sig = W.sig;
   int ord[D];
 #pragma unroll 1
   for (int c = 0; c < D; ++c) ord[c] = c;
@@ -620,7 +624,7 @@ __device__ void qd_polar_block(QdPolarLds<DM, PROD> &W) {
     }
   } else if (t == 0) {
     // a (near) singular environment: thread 0 alone
-    qd_polar_singular<DM, PL>(W.Gc, W.Vc, W.Tm, W.sig, smax, W.Pu);
+    qd_polar_singular<QdPolarLds<DM, PROD>, DM>(W, smax);
   }
   __syncthreads();
 }
