@@ -302,7 +302,10 @@ __device__ __noinline__ void qd_polar_singular(WS &W, double smax) {
 #pragma unroll 1
       for (int rr = 0; rr < D; ++rr) nn += cabs2(Tm[rr * D + kk]);
       nn = sqrt(nn);
-      if (nn > 0.5) {
+      // (the squared remainders of the unit vectors sum to D - kk: one of them reaches this line
+      // also where the space left is too small for any to reach a half)
+      const double line = attempt > 0 && 4 * (D - kk) <= D ? 0.99 * sqrt((double)(D - kk) / D) : 0.5;
+      if (nn > line) {
 #pragma unroll 1
         for (int rr = 0; rr < D; ++rr) Tm[rr * D + kk] = cscale(Tm[rr * D + kk], 1.0 / nn);
         ok = true;
