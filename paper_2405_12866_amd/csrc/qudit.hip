@@ -338,8 +338,8 @@ constexpr int kQdFinBlock = 256;  // four waves; the Jacobi uses one 16-lane row
 // programming on a grid; they map it into 1 +- 0.0125), the others are the Taylor polynomial
 // of 1 / sqrt(Y) about I, whose error is (5 / 16) (I - Y)^3. An input near a multiple of a
 // unitary starts there. The factor is done when every entry of Y - I was below 1e-6 before a
-// step. Returns false when that does not happen (singular values below about 1e-3 |A|_F, or
-// none): the Jacobi SVD takes those.
+// step. Returns false when that does not happen in twelve stages (singular values below about
+// 2e-4 |A|_F, or none), and after eight or ten stages when it cannot: the Jacobi SVD takes those.
 // Bound by the latency of its phases on one work-group, 6-7 stages of about 1600 cycles: the
 // whole finalize takes 12 us for 9 x 9 and 14 us for 16 x 16 environments, against 36 and 66
 // with the Jacobi SVD (some 7 sweeps of 9 or 15 rounds, a barrier each).
@@ -384,7 +384,10 @@ __device__ bool qd_polar_poly(QdPolyLds &S, const c128 *Tm, c128 *Pu) {
   constexpr double kB[4] = {-23.620432, -2.721927, -1.977155, -1.337508};
   constexpr double kC[4] = {17.446152, 0.536546, 0.452616, 0.383853};
   bool near = false;
-  for (int st = 0; st < 12; ++st) {
+  // stage st: 0 to go on, 1 done, -1 left to the SVD (looked for where LOOK is set: the stages that
+  // well-conditioned matrices do not reach have a loop of their own)
+  auto stage = [&](int st, auto look) __attribute__((always_inline)) -> int {
+    constexpr bool LOOK = decltype(look)::value;
     // the last stages in the residual R = I - Y, X <- X + X R (I / 2 + (3 / 8) R): what is added
     // is small, so X stays unitary to the rounding of its entries. The first stage is written in
     // R = I - DM Y, small for a near multiple of a unitary (DM^(1/2) X is close to one).
@@ -433,14 +436,30 @@ __device__ bool qd_polar_poly(QdPolyLds &S, const c128 *Tm, c128 *Pu) {
       }
       put(S.Wm, acc);
     }
-    if (st == 0) {
+    // R has eigenvalues 1 - s^2 (s: the singular values now), so with sum (1 - s^2) s^2 = tr R -
+    // |R|_F^2 below 0.05 every direction has arrived (s near 1) or has s below 0.23, and one that is
+    // there at stage seven needs 0.245 to arrive by the last stage: the matrix is left to the SVD (a
+    // rank-deficient one would go through all twelve stages else). Well-conditioned matrices are
+    // done by then: at stage five the sums cost each of them 0.7 us, the test alone in every
+    // stage's loop 0.3.
+    const bool stuck = LOOK && (st & 1) && !near;
+    if (!LOOK ? st == 0 : stuck) {
+      if (LOOK && plane) {
+        f2 = 0.0;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) f2 += 8 * half + 4 * h + lk == li ? yr[h] : 0.0;
+      }
       f2 = row16_sum(f2);
       f2 += __shfl_xor(f2, 16);
       f2 += __shfl_xor(f2, 32);
-      if (lane == 0 && plane == 0) S.red[half] = f2;
+      if (lane == 0 && (LOOK || plane == 0)) S.red[2 * plane + half] = f2;
     }
     const bool more = __syncthreads_or(!fin || !(e2 < 1e-12));
     if (st == 0) near = S.red[0] + S.red[1] < 0.25;
+    if (stuck) {
+      const double t2 = S.red[2] + S.red[3];
+      if (t2 > 0.9 && t2 - (S.red[0] + S.red[1]) < 0.05) return -1;
+    }
     double a = 1.0, b = 0.5, c = 0.375;
     if (st == 0) {
       if (near) {
@@ -475,13 +494,15 @@ __device__ bool qd_polar_poly(QdPolyLds &S, const c128 *Tm, c128 *Pu) {
       put(S.X, acc);
     }
     __syncthreads();
-    if (!more) {
-      if (in) Pu[er * DM + ec] = cmake(get(S.X, 0, er, ec), get(S.X, 1, er, ec));
-      __syncthreads();
-      return true;
-    }
-  }
-  return false;
+    if (more) return 0;
+    if (in) Pu[er * DM + ec] = cmake(get(S.X, 0, er, ec), get(S.X, 1, er, ec));
+    __syncthreads();
+    return 1;
+  };
+  int r = 0;
+  for (int st = 0; st < 7 && !r; ++st) r = stage(st, std::false_type{});
+  for (int st = 7; st < 12 && !r; ++st) r = stage(st, std::true_type{});
+  return r > 0;
 }
 
 // LDS workspace of one DM x DM polar update.
@@ -924,7 +945,11 @@ struct QdSweeper {
       hipLaunchKernelGGL((k_qd_env<R, dd, int64_t>), dim3(NX * P, ns), dim3(kQdBlock), 0, s, a, as, b, bs, g, P,
                          partials.as<c128>(), sl);
     QFS_HIP(hipGetLastError());
-    return sizeof(R) == 4 || products ? finalize_t<dd, true>(P, k, sl, ns, s) : finalize_t<dd, false>(P, k, sl, ns, s);
+    // an environment of fewer products than it has rows is rank-deficient: the polynomials would
+    // only end with the SVD (not so the mix with the old gate, nor the small matrix of a one-qudit slot)
+    const bool deficient = dd > 2 && beta == 0.0 && g.groups * M < dd * dd && !(kinds && kinds[k] == QFS_GATE_1Q);
+    return (sizeof(R) == 4 || products) && !deficient ? finalize_t<dd, true>(P, k, sl, ns, s)
+                                                      : finalize_t<dd, false>(P, k, sl, ns, s);
   }
   template <int dd, bool PROD>
   int finalize_t(int P, int k, const int32_t *sl, int ns, hipStream_t s) {

@@ -1,4 +1,5 @@
-"""Qudit gate updates of environments with fewer products than rows, about as many, and more."""
+"""Qudit gate updates on both sides of the rule that sends environments of fewer products than
+rows straight to the SVD, and on spectra that the polynomials leave to it after some stages."""
 import numpy as np
 import pytest
 import torch
@@ -33,3 +34,15 @@ def test_products_and_rows(d, n, M, beta, precision):
     s = np.linalg.svd(x, compute_uv=False)
     assert np.max(np.abs(u.conj().T @ u - np.eye(D))) < 1e-13 * min(s[0] / max(s[-1], 1e-300), 10)
     assert abs(np.sum(x.conj() * u).real - s.sum()) < 1e-13 * s.sum()
+
+
+@pytest.mark.parametrize("d", [3, 4])
+@pytest.mark.parametrize("small", [(1e-2,), (1e-3,), (3e-4,), (1e-4,), (1e-6,), (1e-3, 1e-5), (0.3, 1e-2, 1e-4), (1e-5, 1e-5)])
+def test_slow_directions(d, small):
+    D = d * d
+    g = np.random.default_rng(int(-1e3 * np.log(small[-1])) + D)
+    a = (I.haar_unitary(D, g) * np.r_[np.ones(D - len(small)), small]) @ I.haar_unitary(D, g)
+    u = _sweep(d, 2, np.eye(D, dtype=complex), np.ascontiguousarray(a.T), I.haar_unitary(D, g), Q.QFS_PREC_FP64, 0.0)
+    w, s, vh = np.linalg.svd(a)
+    assert np.max(np.abs(u - w @ vh)) < 1e-13 * s[0] / s[-1]
+    assert np.max(np.abs(u.conj().T @ u - np.eye(D))) < 1e-13 * 10
