@@ -28,9 +28,6 @@ namespace {
 
 constexpr int kQdBlock = 256;
 constexpr int kQdMaxP = 64;  // environment partial blocks per (start, row group)
-// Environment blocks of a launch over every start (7 qutrits, 16 starts: 12.0 us a launch with
-// 400, 12.9 with 640, 14.6 with 1100, 18.0 with one item a thread).
-constexpr int kQdEnvBlocks = 400;
 constexpr int kQdMaxDD = 256;  // entries of the largest gate (d = 4: 16 x 16)
 // Jacobi stops when every column pair has |g_p^dagger g_q| <= tol |g_p| |g_q|. The Gram
 // entry of D-long columns carries a rounding error of about D eps |g_p| |g_q| (1e-15 for
@@ -931,13 +928,17 @@ struct QdSweeper {
   int env_t(const cx<R> *a, int64_t as, const cx<R> *b, int64_t bs, int k, const int32_t *sl, int ns,
             hipStream_t s) {
     const QdGeom g = qd_geom(dd, n, M, pairs[2 * k], pairs[2 * k + 1]);
-    // blocks per start and row set: the wave sums of a block's 2 RY D values cost as much as
-    // some five items of a thread, so a launch over every start has about kQdEnvBlocks blocks,
-    // enough to fill the device, and no more (the count follows the call's starts, not those
-    // still running, so a start's sums do not depend on the others)
+    // blocks per start and row set, from the geometry alone, so that a start's sums are the same
+    // whatever runs beside it: a thread's items fall with P while the blocks' wave sums and the
+    // finalize's reads, eight at a time, grow with it, so the best P goes with the root of the
+    // items, and below 16 blocks a start's own chain is what counts. Complex64 sweeps of 1 / 4 / 16
+    // starts at this P, and at P for 400 blocks over the starts: 7 qutrits, M = 64 404 / 466 / 596
+    // us, 417 / 468 / 590; 8 ququarts, M = 32 513 / 1101 / 3548, 516 / 1111 / 3459. With one item a
+    // thread (64 blocks at most) the first take up to 7 % longer.
     constexpr int NX = dd * dd / qd_env_rows<dd>();
-    const int64_t most = std::min<int64_t>(kQdMaxP, (g.groups * M + kQdBlock - 1) / kQdBlock);
-    const int P = (int)std::max<int64_t>(1, std::min<int64_t>(most, (kQdEnvBlocks + NX * S - 1) / (NX * S)));
+    const int64_t most = (g.groups * M + kQdBlock - 1) / kQdBlock;
+    const int64_t root = ((int64_t)std::ceil(2.0 * std::sqrt((double)most)) + 7) / 8 * 8;
+    const int P = (int)std::min<int64_t>(most, std::min<int64_t>(kQdMaxP, std::max<int64_t>(16, root)));
     if (qd_narrow(g, dd))
       hipLaunchKernelGGL((k_qd_env<R, dd, uint32_t>), dim3(NX * P, ns), dim3(kQdBlock), 0, s, a, as, b, bs, g, P,
                          partials.as<c128>(), sl);
