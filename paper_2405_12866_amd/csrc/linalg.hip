@@ -35,9 +35,13 @@ __global__ __launch_bounds__(256) void k_zgemm(int m, int n, int k, c128 alpha, 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int li = lane & 15, lk = lane >> 4;
   // tiles of one row of C on one XCD (consecutive work-groups go round the eight), near in time,
-  // so that its rows of A come from memory once and from that XCD's L2 after
-  const int nx = (n + 31) / 32, seq = blockIdx.x >> 3;
-  const int i0 = ((seq / nx) * 8 + (blockIdx.x & 7)) * 32, j0 = (seq % nx) * 32;
+  // so that its rows of A come from memory once and from that XCD's L2 after; with fewer rows of
+  // tiles than XCDs all of A stays in every L2, and the grid is the tiles alone (padded to eight
+  // rows, 4 x 4 by 4 x 100000 took 130 us, most of it work-groups that leave at once, and
+  // 2^26 columns more work-items than a grid may have)
+  const int ny = (m + 31) / 32, nx = (n + 31) / 32, seq = blockIdx.x >> 3;
+  const int i0 = (ny < 8 ? blockIdx.x % ny : (seq / nx) * 8 + (blockIdx.x & 7)) * 32;
+  const int j0 = (ny < 8 ? blockIdx.x / ny : seq % nx) * 32;
   if (i0 >= m) return;
   // (rows and columns beyond the matrix read its last one; their results are not stored)
   const c128 *ap[2], *bp[2];
@@ -153,7 +157,8 @@ __global__ __launch_bounds__(256) void k_zgemm(int m, int n, int k, c128 alpha, 
 static int zgemm_go(bool conj_a, int m, int n, int k, c128 alpha, ZMat<const c128> A, ZMat<const c128> B, c128 beta,
                     ZMat<c128> C, hipStream_t s) {
   if (m <= 0 || n <= 0) return QFS_OK;
-  const int64_t tiles = ((m + 31) / 32 + 7) / 8 * 8 * (int64_t)((n + 31) / 32);
+  const int ny = (m + 31) / 32;
+  const int64_t tiles = (ny < 8 ? ny : (ny + 7) / 8 * 8) * (int64_t)((n + 31) / 32);
   const dim3 grid((unsigned)tiles);
   if (conj_a)
     hipLaunchKernelGGL(k_zgemm<true>, grid, dim3(256), 0, s, m, n, k, alpha, A, B, beta, C);
