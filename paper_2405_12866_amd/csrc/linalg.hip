@@ -270,6 +270,9 @@ static int gram_splitk(int m, int n, int k, const c128 *A, int lda, const c128 *
 // where one work-group with the panel in LDS and three barriers a step took 45 and 22.
 constexpr int kCholB = 32;
 
+// FULL: b = kCholB, the steps in one run of code. Else (the last panel) the steps from b on, whose
+// rows and columns are not used, are left out: a 3 x 3 matrix would take a whole panel's time.
+template <bool FULL>
 __global__ __launch_bounds__(256) void k_chol_panel(int m, int j, int b, c128 *G, int *flag) {
   __shared__ c128 R[kCholB][kCholB + 1];
   __shared__ double inv[kCholB];
@@ -291,18 +294,20 @@ __global__ __launch_bounds__(256) void k_chol_panel(int m, int j, int b, c128 *G
   }
 #pragma unroll
   for (int jj = 0; jj < kCholB; ++jj) {
-    if (g == (jj & 7)) R[jj][c] = v[jj >> 3];
-    lds_barrier();
-    const double d = R[jj][jj].re;
-    const bool ok = d > 0.0;
-    const double ip = ok ? rsq_nr(d) : 0.0;
-    if (tid == 0) {
-      inv[jj] = ip;
-      if (!ok && blockIdx.x == 0) flag[0] = 1;
-    }
-    const c128 x = cscale(R[jj][c], -ip * ip);
+    if (FULL || jj < b) {
+      if (g == (jj & 7)) R[jj][c] = v[jj >> 3];
+      lds_barrier();
+      const double d = R[jj][jj].re;
+      const bool ok = d > 0.0;
+      const double ip = ok ? rsq_nr(d) : 0.0;
+      if (tid == 0) {
+        inv[jj] = ip;
+        if (!ok && blockIdx.x == 0) flag[0] = 1;
+      }
+      const c128 x = cscale(R[jj][c], -ip * ip);
 #pragma unroll
-    for (int k = jj >> 3; k < 4; ++k) cfma_conj(v[k], x, R[jj][g + 8 * k]);
+      for (int k = jj >> 3; k < 4; ++k) cfma_conj(v[k], x, R[jj][g + 8 * k]);
+    }
   }
   lds_barrier();
   // R_JJ above the diagonal, zero elsewhere; the pivots' roots
@@ -361,7 +366,11 @@ static int cholesky_upper_blocked(int m, c128 *G, int *flag, hipStream_t s) {
   const c128 one = cmake(1.0, 0.0), mone = cmake(-1.0, 0.0);
   for (int j = 0; j < m; j += kCholB) {
     const int b = std::min(kCholB, m - j), rest = m - j - b;
-    hipLaunchKernelGGL(k_chol_panel, dim3((unsigned)std::max(1, (rest + 63) / 64)), dim3(256), 0, s, m, j, b, G, flag);
+    const dim3 grid((unsigned)std::max(1, (rest + 63) / 64));
+    if (b == kCholB)
+      hipLaunchKernelGGL(k_chol_panel<true>, grid, dim3(256), 0, s, m, j, b, G, flag);
+    else
+      hipLaunchKernelGGL(k_chol_panel<false>, grid, dim3(256), 0, s, m, j, b, G, flag);
     QFS_HIP(hipGetLastError());
     if (rest > 0) {
       const c128 *panel = G + (int64_t)j * m + j + b;
