@@ -89,7 +89,10 @@ int launch_t(const CircuitArgs &A, size_t lds, hipStream_t s) {
 
 }  // namespace
 
-bool circuit_fits(int n) { return n >= 2 && n <= kCircuitMaxBits; }
+// LDS of a work-group with 2^bits amplitudes
+static size_t circuit_lds(int bits) { return sizeof(c128) * ((size_t(1) << bits) + ((size_t(1) << bits) >> 4)); }
+
+bool circuit_fits(int n) { return n >= 2 && n <= kCircuitMaxBits && circuit_lds(n) <= lds_max_bytes(); }
 
 int launch_circuit(int n, int M, const c128 *src, c128 *dst, int64_t si, int64_t sj, int L, const int32_t *pairs,
                    const c128 *gates, bool dagger, hipStream_t s) {
@@ -97,7 +100,7 @@ int launch_circuit(int n, int M, const c128 *src, c128 *dst, int64_t si, int64_t
   // one group of four amplitudes per thread and gate: 1024 threads where a state alone has as
   // many groups or the set fills the device with such work-groups; else 256, so that small
   // sets spread over more compute units
-  const bool wide = n >= 12 || (int64_t)M << n >= int64_t(256) * 4096;
+  const bool wide = n >= 12 || ((int64_t)M << n >= int64_t(256) * 4096 && circuit_lds(12) <= lds_max_bytes());
   const int groups_log = wide ? 12 : 10;  // amplitudes of a work-group
   CircuitArgs A{};
   A.dst = dst;
@@ -107,8 +110,7 @@ int launch_circuit(int n, int M, const c128 *src, c128 *dst, int64_t si, int64_t
   A.M = M;
   A.lspw = std::max(0, groups_log - n);
   while (A.lspw > 0 && (int64_t(1) << (A.lspw - 1)) >= M) --A.lspw;
-  const uint32_t amps = 1u << (n + A.lspw);
-  const size_t lds = sizeof(c128) * (amps + (amps >> 4));
+  const size_t lds = circuit_lds(n + A.lspw);
   for (int t0 = 0; t0 == 0 || t0 < L; t0 += kCircuitGates) {
     A.src = t0 == 0 ? src : dst;
     A.L = std::min(kCircuitGates, L - t0);

@@ -46,6 +46,17 @@ int ensure_dynamic_lds(const void *fn, size_t bytes, size_t *have) {
   return QFS_OK;
 }
 
+size_t lds_max_bytes() {
+  static const size_t cached = [] {  // (initialised once, thread-safe)
+    int dev = 0, v = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && v > 0)
+      return (size_t)v;
+    return (size_t)64 * 1024;
+  }();
+  return cached;
+}
+
 // Device blocks kept between calls, by device and exact size, in the order they came back.
 // hipMalloc of the large working sets and hipFree (which drains the device) otherwise cost
 // several hundred microseconds each in every call, during which the device idles. The cache
@@ -275,17 +286,6 @@ int ceil_log2(int64_t x) {
 // Row-major N x ld masters (states as columns) use ld = 2^ceil(log2 max(M, 2)), so
 // that the same buffer is also a one-chunk set of the chunked layout.
 int master_ld(int M) { return 1 << std::max(1, ceil_log2(std::max(M, 2))); }
-
-size_t lds_max_bytes() {
-  static const size_t cached = [] {  // (initialised once, thread-safe)
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && v > 0)
-      return (size_t)v;
-    return (size_t)64 * 1024;
-  }();
-  return cached;
-}
 
 int validate_template(const qfs_template *t) {
   if (!t || t->n_qubits < 2 || t->n_qubits > 24 || t->n_gates < 1 || !t->pairs) {

@@ -208,7 +208,8 @@ struct DevBuf {
 // ------------------------------------------------------------------ kernels (host API)
 // The gates of a list applied in order (dagger: u^dagger, last gate first) to M FP64 states in
 // one launch (circuit.hip): element (amplitude i, sample j) of src and dst (which may be the
-// same) at i si + j sj, one of si and sj being 1. For 2 to 13 qubits (circuit_fits).
+// same) at i si + j sj, one of si and sj being 1. For 2 to 13 qubits, as far as a state fits a
+// work-group's LDS (circuit_fits).
 bool circuit_fits(int n);
 int launch_circuit(int n, int M, const c128 *src, c128 *dst, int64_t si, int64_t sj, int L, const int32_t *pairs,
                    const c128 *gates, bool dagger, hipStream_t s);
@@ -220,6 +221,7 @@ enum { kRoleTrain = 1, kRoleVal = 2, kRoleInit = 3 };
 // for per kernel); *have caches what was set. Serialised across threads: problems may be
 // run from several host threads at once.
 int ensure_dynamic_lds(const void *fn, size_t bytes, size_t *have);
+size_t lds_max_bytes();  // LDS a work-group of the device may have (64 KiB where it does not say)
 int launch_ginibre(int64_t rows, int64_t col0, int64_t col1, int64_t ld, uint64_t seed,
                    uint32_t role, uint32_t stream, c128 *A, hipStream_t s);
 int launch_haar_gates(uint64_t seed, int32_t start0, int32_t starts, int32_t L, c128 *out,
