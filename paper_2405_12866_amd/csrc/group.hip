@@ -152,11 +152,12 @@ constexpr int kMaxPkt = 2048 / kGBlock;
 
 // DIST selects the distance pass (the last group's operator applied to the state, then
 // sum |a - b|^2) instead of the environment pass; each has its own kernel, so neither
-// carries the other's registers. Four waves a SIMD: the FP64 pass then spills ten registers
-// outside its tile loop's products, and takes 23.3 us (11 qubits, M = 100, 5 starts) instead
-// of the 24.5 of three waves; the FP32 one needs no more than 116 anyway.
+// carries the other's registers. Three waves a SIMD for FP64: held to four it spills ten registers,
+// and FP64 sweeps of 12 qubits, M = 256, 16 starts take 2.97 ms instead of 2.65, of 11 qubits and 16
+// starts 785 us instead of 737 (M = 100), of 9 qubits and 5 starts 246 instead of 229. The FP32 one
+// needs 116 registers and fits four.
 template <typename R, bool DIST>
-__global__ __launch_bounds__(kGBlock, 4) void k_bwd_group(GroupArgs<R> A) {
+__global__ __launch_bounds__(kGBlock, sizeof(R) == 8 ? 3 : 4) void k_bwd_group(GroupArgs<R> A) {
   constexpr int V = Pk<R>::V, LOGV = Pk<R>::LOGV;
   using MF = Mfma<R>;
   using acc_t = typename MF::acc_t;
