@@ -62,10 +62,13 @@ const char *qfs_version(void);
  * device buffers, up to an eighth of the device's memory in all (the oldest are freed beyond
  * that), and reuses them in later calls that need buffers of like sizes, instead of freeing
  * and allocating them again. An allocation that fails frees the kept buffers first, and the
- * free-memory budget of a call counts them as free. This frees the buffers kept for the
- * current device and stores their total size in *bytes_freed (may be null). Blocks are
- * kept only once the work that used them has ended, so it may be called at any time, from
- * any thread. Returns QFS_OK or QFS_EDEVICE. */
+ * free-memory budget of a call counts them as free. Inside a call, qudit runs free the large
+ * buffers of a stage that is over (a doubling, the switch of precision, a group of starts)
+ * before they go on, the batched engine a scratch that it replaces, and either all of them
+ * when the call has a device_mem_budget. This frees the buffers kept for the current device
+ * and stores their total size in *bytes_freed (may be null). Blocks are kept only once the
+ * work that used them has ended, so it may be called at any time, from any thread. Returns
+ * QFS_OK or QFS_EDEVICE. */
 int qfs_release_device_cache(size_t *bytes_freed);
 
 /* ---------------------------------------------------------------- problem */

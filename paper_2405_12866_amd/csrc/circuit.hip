@@ -29,8 +29,10 @@ __device__ __forceinline__ uint32_t amp_slot(uint32_t i) { return i + (i >> 4); 
 
 // Bound by FP64 issue and LDS throughput alike (a gate is 16 complex FMAs, four 16-byte reads
 // and four writes per group of four amplitudes) and by the barrier after each gate: 12 qubits,
-// 256 states, 44 gates in 57 us (1.3 us a gate on every compute unit, 19 us of FP64 issue in
+// 256 states, 44 gates in 55 us (1.3 us a gate on every compute unit, 19 us of FP64 issue in
 // all), against 44 launches of 9.0 us, and 14 us of layout conversions, with one gate a launch.
+// That is a caller's set, rows of amplitudes. A run's sets have the samples contiguous: with one
+// sample a work-group each 16-byte read then takes a whole line, and the same launch 82 us.
 template <int T, bool DAG>
 __global__ __launch_bounds__(T) void k_circuit(CircuitArgs A) {
   extern __shared__ __align__(16) unsigned char lds_raw[];

@@ -331,7 +331,8 @@ constexpr int kQdFinBlock = 256;  // four waves; the Jacobi uses one 16-lane row
 // FP64 matrix cores, one real product per wave (plane re / im of the result, half of the
 // inner index), so a stage is three phases of four 16x16x4 products a wave and a barrier.
 // Scaled by |A|_F the singular values lie in (0, 1]; the first four polynomials minimise
-// max |1 - p| over the interval the one before leaves, from [0.01, 1] on (found by linear
+// max |1 - p| over the interval the one before leaves, from [0.01, 1] on (composed minimax
+// polynomials as in Amsel, Persson, Musco and Gower, The Polar Express, 2025; these found by linear
 // programming on a grid; they map it into 1 +- 0.0125), the others are the Taylor polynomial
 // of 1 / sqrt(Y) about I, whose error is (5 / 16) (I - Y)^3. An input near a multiple of a
 // unitary starts there. The factor is done when every entry of Y - I was below 1e-6 before a
